@@ -29,6 +29,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <mutex>
 #include <thread>
 #include <vector>
 
@@ -296,6 +297,8 @@ struct bs_mesh {
     std::vector<double> xyz, omega; // current FP64 inputs
     double hbar = 0.0, max_vc = 0.0;
     double max_abs = 0.0; // largest coordinate magnitude of any node or evaluation point
+    double extent = 0.0;  // diagonal of the bounding box of the nodes and evaluation points
+    double max_w = 0.0;   // largest magnitude of any component of a Gauss point's strength
     int64_t reoriented = 0;
     std::vector<int8_t> orient; // sign of det per tet at upload (inversion check on updates)
     std::vector<int32_t> h_rank, h_order, h_cell_start; // node rank, tet order, bins (host copies)
@@ -1062,6 +1065,7 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
     m->tnblk = tnblk;
     std::vector<float> xh((size_t)3 * npad), xl((size_t)3 * npad), om((size_t)3 * npad);
     double max_abs = 0.0;
+    double xlo[3] = {1e300, 1e300, 1e300}, xhi[3] = {-1e300, -1e300, -1e300};
     for (int64_t p = 0; p < npad; ++p) {
         const bool is_t = p >= t0 && p < t0 + tn;
         const int64_t i = p < n ? orig[(size_t)p] : is_t ? torig[(size_t)(p - t0)] : (n > 0 ? orig[0] : 0);
@@ -1069,6 +1073,8 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
             const double x = is_t ? m->tgt[3 * i + c] : (n > 0 ? X[3 * i + c] : 0.0);
             const float h = (float)x;
             max_abs = std::max(max_abs, std::fabs(x));
+            xlo[c] = std::min(xlo[c], x);
+            xhi[c] = std::max(xhi[c], x);
             xh[(size_t)c * npad + p] = h;
             xl[(size_t)c * npad + p] = (float)(x - (double)h);
             om[(size_t)c * npad + p] = (is_t || n == 0) ? 0.f : (float)W[3 * i + c];
@@ -1139,6 +1145,9 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
     }
     m->max_vc = max_vc;
     m->max_abs = max_abs;
+    m->extent = npad > 0 ? std::sqrt((xhi[0] - xlo[0]) * (xhi[0] - xlo[0]) + (xhi[1] - xlo[1]) * (xhi[1] - xlo[1]) +
+                                     (xhi[2] - xlo[2]) * (xhi[2] - xlo[2]))
+                         : 0.0;
     bsk::Bins bins{};
     double cs = 2.0 * (m->hbar > 0 ? m->hbar : 1.0);
     if (T > 0) {
@@ -1190,7 +1199,10 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
     std::vector<int4> &tid = m->h_tid;
     tid.resize((size_t)T);
     const TetRule R1 = tet_rule(1), R4 = tet_rule(4), R11 = tet_rule(11);
+    std::mutex w_mutex;
+    double max_w = 0.0;
     parallel_for(T, [&](int64_t a, int64_t b) {
+        double mw = 0.0;
         for (int64_t k = a; k < b; ++k) {
             const int64_t t = order[(size_t)k];
             const int32_t *id = &m->tets[4 * t];
@@ -1219,6 +1231,7 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
                     for (int c = 0; c < 3; ++c) {
                         dst[8 * q + c] = (float)p[c];
                         dst[8 * q + 3 + c] = (float)(f * o[c]);
+                        mw = std::max(mw, std::fabs(f * o[c]));
                     }
                     dst[8 * q + 6] = 0.f;
                     dst[8 * q + 7] = 0.f;
@@ -1232,7 +1245,10 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
             tid[(size_t)k] = make_int4(rank[(size_t)id[0]], rank[(size_t)id[1]], rank[(size_t)id[2]],
                                        rank[(size_t)id[3]]);
         }
+        std::lock_guard<std::mutex> lock(w_mutex);
+        max_w = std::max(max_w, mw);
     });
+    m->max_w = max_w;
     // the records (most of the bytes uploaded) go to the device now, from
     // pinned memory, while the host builds the rest; every later return
     // first waits for these copies (the staging is rewritten by the next
@@ -1773,6 +1789,30 @@ struct EvalBufs {
     int *nonfinite, *fallback, *sel;
 };
 
+// Scales of the split contraction (bs_split_dev.h) for pairs no closer than
+// `cut`, whose scaled distance is at least 2^-5, so that d^-3 <= 2^15, and
+// for strengths times offsets up to 2^15: both fit binary16.  eps: relative
+// margin on d^2 around the cut.  Its low pieces lose bits below 2^-24, which
+// is 2^-36 of the largest d^-3 or less; out to 128 cuts (d^-3 down to 2^-21
+// of the largest) a pair's loss stays below 2^-13 of the rounding error of
+// one pair at the cut.  Larger extents, vanishing cuts and strengths outside
+// binary32's normal range keep the binary32 contraction (xs = 0).
+void split_scales(const bs_mesh *m, double cut, double eps, bsk::Thresholds &th)
+{
+    th.xs = th.ws = th.d2_g1 = th.d2_amb = 0.f;
+    if (!(cut > 1e-12) || !(cut < 1e12) || !(eps < 0.5) || !(m->extent <= 128.0 * cut) || !(m->max_w < 1e25)) return;
+    int k = 0;
+    std::frexp(cut, &k); // cut in [2^(k-1), 2^k)
+    const double xs = std::ldexp(1.0, -k - 4);
+    const double top = std::max(m->max_w, 1e-25) * std::max(1.0, m->extent * xs);
+    int kw = 0;
+    std::frexp(top, &kw); // top < 2^kw
+    th.xs = (float)xs;
+    th.ws = (float)std::ldexp(1.0, 14 - kw);
+    th.d2_g1 = (float)(cut * xs * cut * xs * (1.0 + eps));
+    th.d2_amb = (float)(cut * xs * cut * xs * (1.0 - eps));
+}
+
 // One evaluation into m->vel (device, input node order), on stream s.
 // targets: the evaluation points after the nodes (bs_eval_points) instead
 // of the nodes; their velocities go to m->tvel.  With given buffers (nodes
@@ -1833,6 +1873,7 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, const EvalBufs *given =
             th.s_g1 = 0.f;
             th.s_amb = INFINITY;
         }
+        split_scales(m, c_4, eps, th);
     }
     bsk::AngTab ang{};
     ang.dir = (const float4 *)m->dir.p;

@@ -50,6 +50,11 @@ struct Thresholds {
     // surely beyond the G4 cut by the rule's binary32 test, above s_amb surely
     // within it; between them (or NaN) the rule's test decides
     float s_g1, s_amb;
+    // the split contraction (bs_split_dev.h): positions are scaled by xs and
+    // strengths by ws, powers of two; its bounds on the scaled d^2 (above
+    // d2_g1 surely beyond the G4 cut, below d2_amb surely within it).
+    // xs == 0: the operands do not fit its number range
+    float xs, ws, d2_g1, d2_amb;
 };
 
 struct AngTab {

@@ -34,6 +34,7 @@
 //   k_combine    FP64 sum of the partials, back to input node order.
 #include "bs_internal.h"
 #include "bs_mlp_dev.h"
+#include "bs_split_dev.h"
 
 #include <hip/hip_runtime.h>
 
@@ -335,7 +336,74 @@ struct FarLds {
     float4 nts[4];                            // bounding sphere of each node tile (radius < 0: no node)
 };
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+// Block and tet split of this workgroup.  Consecutive workgroup ids go to the
+// eight XCDs in turn.  With fewer than eight splits: id = block * splits +
+// split.  With 8 S splits: XCD x = id % 8 owns the splits x S .. x S + S - 1
+// (one eighth of the tets) and takes them one after the other, every block
+// on a split before the next (id / 8 = sub * nblk + block), so the split's
+// records (sized to fit the XCD's L2 by the host) are read by all blocks
+// while resident.
+__device__ __forceinline__ void far_item(int splits, int nblk, int &bl, int &split)
+{
+    if (splits >= 8) {
+        const int per_xcd = splits >> 3;
+        const int rest = (int)(blockIdx.x >> 3);
+        const int sub = rest / nblk;
+        bl = rest - sub * nblk;
+        split = (int)(blockIdx.x & 7) * per_xcd + sub;
+    } else {
+        bl = blockIdx.x / splits;
+        split = blockIdx.x - bl * splits;
+    }
+}
+
+// The block's binary32 node coordinates and the bounding sphere of each of
+// its four node tiles (radius < 0: no node), by the whole workgroup.
+__device__ __forceinline__ void far_node_spheres(const DevMesh &m, int b, int tid, float4 *xn, float4 *nts)
+{
+    if (tid < 64) {
+        const int i = b * kBlockNodes + tid;
+        xn[tid] = make_float4(m.xh[i], m.xh[m.npad + i], m.xh[2 * m.npad + i], 0.f);
+    }
+    __syncthreads();
+    if (tid < 4) {
+        float lo[3] = {3e38f, 3e38f, 3e38f}, hi[3] = {-3e38f, -3e38f, -3e38f};
+        const int nv = min(16, m.nv - (b * kBlockNodes + 16 * tid));
+        for (int k = 0; k < nv; ++k) {
+            const float4 x = xn[16 * tid + k];
+            lo[0] = fminf(lo[0], x.x), hi[0] = fmaxf(hi[0], x.x);
+            lo[1] = fminf(lo[1], x.y), hi[1] = fmaxf(hi[1], x.y);
+            lo[2] = fminf(lo[2], x.z), hi[2] = fmaxf(hi[2], x.z);
+        }
+        const float cx = 0.5f * (lo[0] + hi[0]), cy = 0.5f * (lo[1] + hi[1]), cz = 0.5f * (lo[2] + hi[2]);
+        float r2 = 0.f;
+        for (int k = 0; k < nv; ++k) {
+            const float4 x = xn[16 * tid + k];
+            const float dx = x.x - cx, dy = x.y - cy, dz = x.z - cz;
+            r2 = fmaxf(r2, (dx * dx + dy * dy) + dz * dz);
+        }
+        nts[tid] = nv > 0 ? make_float4(cx, cy, cz, sqrtf(r2) * (1.f + 1e-5f) + 1e-6f) : make_float4(0.f, 0.f, 0.f, -1.f);
+    }
+    __syncthreads();
+}
+
+// v = S x x' - U of node tid of block b from its six sums sw = [S, U].
+__device__ __forceinline__ void far_assemble(const DevMesh &m, int b, int tid, const float4 &bc, const double (&sw)[6],
+                                             double *__restrict__ o)
+{
+    const int i = b * kBlockNodes + tid;
+    double xp[3] = {0.0, 0.0, 0.0};
+    if (i < m.nv) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const float cc = c == 0 ? bc.x : c == 1 ? bc.y : bc.z;
+            xp[c] = (double)((m.xh[c * m.npad + i] - cc) + m.xl[c * m.npad + i]);
+        }
+    }
+    o[i] = (sw[1] * xp[2] - sw[2] * xp[1]) - sw[3];
+    o[m.npad + i] = (sw[2] * xp[0] - sw[0] * xp[2]) - sw[4];
+    o[2 * m.npad + i] = (sw[0] * xp[1] - sw[1] * xp[0]) - sw[5];
+}
 
 template <int PREC>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_far_mfma(DevMesh m, Thresholds th, int splits,
@@ -346,23 +414,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q = lane >> 4, i16 = lane & 15, c4 = lane & 3;
-    // Consecutive workgroup ids go to the eight XCDs in turn.  With fewer
-    // than eight splits: id = block * splits + split.  With 8 S splits: XCD
-    // x = id % 8 owns the splits x S .. x S + S - 1 (one eighth of the tets)
-    // and takes them one after the other, every block on a split before the
-    // next (id / 8 = sub * nblk + block), so the split's records (sized to
-    // fit the XCD's L2 by the host) are read by all blocks while resident.
     int bl, split;
-    if (splits >= 8) {
-        const int per_xcd = splits >> 3;
-        const int rest = (int)(blockIdx.x >> 3);
-        const int sub = rest / m.nblk;
-        bl = rest - sub * m.nblk;
-        split = (int)(blockIdx.x & 7) * per_xcd + sub;
-    } else {
-        bl = blockIdx.x / splits;
-        split = blockIdx.x - bl * splits;
-    }
+    far_item(splits, m.nblk, bl, split);
     const int b = m.blk0 + bl;
     const int t0 = split * per_split;
     const int t1 = min(m.T, t0 + per_split);
@@ -382,33 +435,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
         B1[nt] = q == 0 ? xp[0] : q == 1 ? xp[1] : q == 2 ? xp[2] : 1.f;
         Cin[nt] = i < m.nv ? (xp[0] * xp[0] + xp[1] * xp[1]) + xp[2] * xp[2] : 1e30f;
     }
-    if (tid < 64) {
-        const int i = b * kBlockNodes + tid;
-        S.xn[tid] = make_float4(m.xh[i], m.xh[m.npad + i], m.xh[2 * m.npad + i], 0.f);
-    }
-    __syncthreads();
-    if (tid < 4) {
-        float lo[3] = {3e38f, 3e38f, 3e38f}, hi[3] = {-3e38f, -3e38f, -3e38f};
-        const int nv = min(16, m.nv - (b * kBlockNodes + 16 * tid));
-        for (int k = 0; k < nv; ++k) {
-            const float4 x = S.xn[16 * tid + k];
-            lo[0] = fminf(lo[0], x.x), hi[0] = fmaxf(hi[0], x.x);
-            lo[1] = fminf(lo[1], x.y), hi[1] = fmaxf(hi[1], x.y);
-            lo[2] = fminf(lo[2], x.z), hi[2] = fmaxf(hi[2], x.z);
-        }
-        const float cx = 0.5f * (lo[0] + hi[0]), cy = 0.5f * (lo[1] + hi[1]), cz = 0.5f * (lo[2] + hi[2]);
-        float r2 = 0.f;
-        for (int k = 0; k < nv; ++k) {
-            const float4 x = S.xn[16 * tid + k];
-            const float dx = x.x - cx, dy = x.y - cy, dz = x.z - cz;
-            r2 = fmaxf(r2, (dx * dx + dy * dy) + dz * dz);
-        }
-        S.nts[tid] = nv > 0 ? make_float4(cx, cy, cz, sqrtf(r2) * (1.f + 1e-5f) + 1e-6f) : make_float4(0.f, 0.f, 0.f, -1.f);
-    }
-    __syncthreads();
-    float4 nts[4];
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) nts[nt] = S.nts[nt];
+    far_node_spheres(m, b, tid, S.xn, S.nts);
 
     f32x4 D0[4], D1[4];
 #pragma unroll
@@ -605,19 +632,206 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
 #pragma unroll
             for (int w = 0; w < 4; ++w) sw[r] += (double)S.accs[w][r][tid] + (double)S.accc[w][r][tid];
         }
-        const int i = b * kBlockNodes + tid;
-        double xp[3] = {0.0, 0.0, 0.0};
-        if (i < m.nv) {
+        far_assemble(m, b, tid, bc, sw, part + (size_t)split * 3 * m.npad);
+    }
+}
+
+// The same far field on the 16-bit matrix instructions (bs_split_dev.h), for
+// every mesh and policy whose distances and strengths fit its number range
+// (Thresholds::xs, set on the host).  Workgroup, splits, chunks, prefetch and
+// band flags as in k_far_mfma; a wave takes units of 32 tets (two per chunk)
+// against the block's four node tiles, and its binary32 sums are folded into
+// the workgroup's compensated sums every fourth chunk (16 accumulations), the
+// waves in turn.  Two-ring mesh (531,441 nodes, 3,072,000 tets): 412 ms
+// against k_far_mfma's 508.  Bound by issue: per 1024 pairs and SIMD about
+// 390 cycles of vector instructions for the cubes and their pieces, 192 of
+// MFMA, 110 for preparing the operands, partly overlapped (635 in all).
+// Relative L2 error against the FP64 oracle (fixed rule, all kernels;
+// k_far_mfma in brackets): ring 6.5e-8 (6.7e-8), two rings 5.8e-8 (6.0e-8),
+// Fourier field 8.7e-8 (8.6e-8).  Measured and left: five waves per SIMD
+// (96 registers, spilled: +14%), raised wave priority at the MFMAs (+1%), two
+// blocks per workgroup around a common centre (spilled: +46%), the distances
+// on v_mfma_f32_16x16x4f32 (+5%).
+struct FarSplitLds {
+    SplitUnit u[2][kFarChunk / 32];
+    unsigned band[2][16];      // [buf][tile]: bit nt = within the band of node tile nt
+    float accs[6][64];         // [register of split_gather][lane]: compensated FP32 sums (value, error)
+    float accc[6][64];
+    float4 xn[64];             // binary32 node coordinates (the rule's), by node
+    float4 nts[4];             // bounding sphere of each node tile (radius < 0: no node)
+};
+
+template <int PREC>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_far_split(DevMesh m, Thresholds th, int splits,
+                                                   int per_split, double *__restrict__ part)
+{
+    constexpr int NT = 4;
+    __shared__ FarSplitLds S;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int q = lane >> 4, i16 = lane & 15;
+    int bl, split;
+    far_item(splits, m.nblk, bl, split);
+    const int b = m.blk0 + bl;
+    const float4 bc = m.blk[b];
+    const int t0 = split * per_split;
+    const int t1 = min(m.T, t0 + per_split);
+    const float xs = th.xs;
+    const int row = split_row(i16);
+    far_node_spheres(m, b, tid, S.xn, S.nts);
+
+    SplitTarget B1[NT];
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const float cc = c == 0 ? bc.x : c == 1 ? bc.y : bc.z;
-                xp[c] = (double)((m.xh[c * m.npad + i] - cc) + m.xl[c * m.npad + i]);
+    for (int nt = 0; nt < NT; ++nt) {
+        const int i = b * kBlockNodes + 16 * nt + i16;
+        const bool in = i < m.nv;
+        float xp[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const float cc = c == 0 ? bc.x : c == 1 ? bc.y : bc.z;
+            xp[c] = in ? ((m.xh[c * m.npad + i] - cc) + m.xl[c * m.npad + i]) * xs : 0.f;
+        }
+        const float x2 = in ? (xp[0] * xp[0] + xp[1] * xp[1]) + xp[2] * xp[2] : 1e30f;
+        B1[nt] = split_target(xp[0], xp[1], xp[2], x2, q);
+    }
+    f32x4 D[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) D[nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int r = wave; r < 6; r += 4) S.accs[r][lane] = S.accc[r][lane] = 0.f;
+
+    float4 pg, ps; // record of tet c0 + tid; bounding sphere of tile lane / NT of the wave's
+    float2 pw;
+    int pt;
+    auto load = [&](int c0) {
+        pt = c0 + tid;
+        const int t = min(pt, t1 - 1);
+        const float *g = m.g1 + (size_t)t * kRecG;
+        pg = *(const float4 *)g;
+        pw = *(const float2 *)(g + 4);
+        ps = m.tsph[min(pt - lane + 16 * (lane / NT & 3), t1 - 1) >> 4];
+    };
+    auto store = [&](int buf) {
+        split_store(S.u[buf][tid >> 5], tid & 31, (pg.x - bc.x) * xs, (pg.y - bc.y) * xs, (pg.z - bc.z) * xs,
+                    pg.w * th.ws, pw.x * th.ws, pw.y * th.ws, pt < t1);
+        // the wave's 64 tets are tiles 4 wave + tl of the chunk; lane
+        // NT tl + nt tests the bounding sphere of tile tl against node
+        // tile nt (a tile past the split repeats the last one: its
+        // strengths are zero)
+        const float4 ns = S.nts[lane % NT];
+        const float dx = ps.x - ns.x, dy = ps.y - ns.y, dz = ps.z - ns.z;
+        const float rr = (ps.w + ns.w + th.r_band) * (1.f + 1e-5f);
+        const bool near = ns.w >= 0.f && (dx * dx + dy * dy) + dz * dz < rr * rr;
+        const unsigned bal = (unsigned)__ballot(near);
+        if (lane < 4) S.band[buf][4 * wave + lane] = (bal >> (NT * lane)) & ((1u << NT) - 1u);
+    };
+    auto fold = [&]() {
+        float y[6];
+        split_gather(D, y);
+#pragma unroll
+        for (int r = 0; r < 6; ++r) {
+            const float a = S.accs[r][lane];
+            const float t = a + y[r];
+            const float bp = t - a;
+            const float e = (a - (t - bp)) + (y[r] - bp);
+            S.accs[r][lane] = t;
+            S.accc[r][lane] += e;
+        }
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) D[nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    };
+
+    if (t0 < t1) {
+        load(t0);
+        store(0);
+        if (t0 + kFarChunk < t1) load(t0 + kFarChunk);
+    }
+    __syncthreads();
+    int k = 0;
+    for (int c0 = t0; c0 < t1; c0 += kFarChunk, ++k) {
+        const int buf = k & 1;
+        if (c0 + kFarChunk < t1) {
+            store(buf ^ 1);
+            if (c0 + 2 * kFarChunk < t1) load(c0 + 2 * kFarChunk);
+        }
+#pragma unroll 1
+        for (int un = wave; un < kFarChunk / 32; un += 4) {
+            const SplitUnit &U = S.u[buf][un];
+            const unsigned bm = __builtin_amdgcn_readfirstlane((int)(S.band[buf][2 * un] | S.band[buf][2 * un + 1]));
+            const bf16x8 A1[2] = {split_load1(U, 0, q, i16), split_load1(U, 1, q, i16)};
+            const f16x8 A2 = split_load2(U, q, row);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const f32x4 ra = split_d2(A1[0], B1[nt]);
+                const f32x4 rb = split_d2(A1[1], B1[nt]);
+                float iv[8];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    iv[j] = __builtin_amdgcn_rsqf(ra[j]);
+                    iv[4 + j] = __builtin_amdgcn_rsqf(rb[j]);
+                }
+                if ((bm >> nt) & 1u) {
+                    // the matrix-core distance decides the pairs clear of
+                    // the G4 cut; a wave with a pair near it (or with
+                    // incidence to test) takes the rule's own test for all
+                    // its pairs
+                    bool g1[8], amb = false;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const float r2 = j < 4 ? ra[j & 3] : rb[j & 3];
+                        g1[j] = r2 > th.d2_g1;
+                        amb = amb || (!g1[j] && !(r2 < th.d2_amb));
+                    }
+                    if (th.inc_far || __ballot(amb)) {
+                        const float4 xn = S.xn[16 * nt + i16];
+                        const int self = b * kBlockNodes + 16 * nt + i16;
+                        unsigned bits = 0;
+#pragma unroll 1
+                        for (int j = 0; j < 8; ++j) {
+                            // (a slot past the split reads the last tet: its
+                            // strength is zero, any decision holds)
+                            const int tg = min(c0 + un * 32 + 16 * (j >> 2) + 4 * q + (j & 3), t1 - 1);
+                            const float4 pc = *reinterpret_cast<const float4 *>(m.g1 + (size_t)tg * kRecG);
+                            const float dx = xn.x - pc.x, dy = xn.y - pc.y, dz = xn.z - pc.z;
+                            const float sx = dx * dx, sy = dy * dy, sz = dz * dz;
+                            bool on = !((sx + sy) + sz < th.g4_2);
+                            if (th.inc_far) {
+                                const int4 id = m.tid[tg];
+                                on = on && !((id.x == self) | (id.y == self) | (id.z == self) | (id.w == self));
+                            }
+                            bits |= on ? 1u << j : 0u;
+                        }
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) g1[j] = (bits >> j) & 1u;
+                    }
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) iv[j] = g1[j] ? iv[j] : 0.f;
+                }
+                f16x8 h, l;
+                split_cubes(iv, h, l);
+                D[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A2, h, D[nt], 0, 0, 0);
+                D[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A2, l, D[nt], 0, 0, 0);
             }
         }
-        double *o = part + (size_t)split * 3 * m.npad;
-        o[i] = (sw[1] * xp[2] - sw[2] * xp[1]) - sw[3];
-        o[m.npad + i] = (sw[2] * xp[0] - sw[0] * xp[2]) - sw[4];
-        o[2 * m.npad + i] = (sw[0] * xp[1] - sw[1] * xp[0]) - sw[5];
+        if (PREC == 1 && (k & 3) == wave) fold();
+        __syncthreads();
+    }
+    for (int w = 0; w < 4; ++w) {
+        if (w == wave) fold();
+        __syncthreads();
+    }
+    if (tid < 64) {
+        // the scaled sums back to the mesh's units: s by xs^3, the offsets
+        // in the last three components by 1 / xs, the strengths by 1 / ws
+        const double f = (double)xs * (double)xs * (double)xs / (double)th.ws;
+        double sw[6];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+            int ln;
+            const int r = split_slot(c, tid, ln);
+            sw[c] = ((double)S.accs[r][ln] + (double)S.accc[r][ln]) * (c < 3 ? f : f / (double)xs);
+        }
+        far_assemble(m, b, tid, bc, sw, part + (size_t)split * 3 * m.npad);
     }
 }
 
@@ -627,10 +841,16 @@ hipError_t launch_far_mfma(const DevMesh &m, const Thresholds &th, int precision
     if (splits < 1 || (splits > 8 && splits % 8) || precision < 0 || precision > 1) return hipErrorInvalidValue;
     const int per = ((m.T + splits - 1) / splits + kFarChunk - 1) / kFarChunk * kFarChunk;
     const dim3 grid(m.nblk * splits);
-    if (precision == 0)
+    if (th.xs > 0.f) {
+        if (precision == 0)
+            hipLaunchKernelGGL(k_far_split<0>, grid, dim3(256), 0, s, m, th, splits, per, part);
+        else
+            hipLaunchKernelGGL(k_far_split<1>, grid, dim3(256), 0, s, m, th, splits, per, part);
+    } else if (precision == 0) {
         hipLaunchKernelGGL(k_far_mfma<0>, grid, dim3(256), 0, s, m, th, splits, per, part);
-    else
+    } else {
         hipLaunchKernelGGL(k_far_mfma<1>, grid, dim3(256), 0, s, m, th, splits, per, part);
+    }
     return hipGetLastError();
 }
 
