@@ -1341,7 +1341,7 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
         (rc = dalloc(m->blk, sizeof(float4) * blk.size())) || (rc = dalloc(m->node_orig, 4 * (size_t)n)) ||
         (rc = dalloc(m->torig, 4 * torig.size())) || (rc = dalloc(m->tlist, 4 * tlist.size())) ||
         (rc = dalloc(m->tvel, 8 * 3 * (size_t)tn)) || (rc = dalloc(m->tid, sizeof(int4) * (size_t)T)) ||
-        (rc = dalloc(m->cell_start, 4 * cell_start.size())) || (rc = dalloc(m->band, 8 * 3 * (size_t)npad)) ||
+        (rc = dalloc(m->cell_start, 4 * cell_start.size())) ||
         (rc = dalloc(m->rtv, 8 * 3 * (size_t)npad)) || (rc = dalloc(m->vel, 8 * 3 * (size_t)n)) ||
         (rc = dalloc(m->cnt, 8 * bsk::kCntWords)) || (rc = dalloc(m->nonfinite, 4)) ||
         (rc = dalloc(m->nbr, sizeof(int4) * (size_t)T)) ||
@@ -1780,10 +1780,29 @@ int far_splits(const bs_mesh *m)
     return std::max(1, std::min<int>((int)((4096 + 4 * node_blocks - 1) / (4 * node_blocks)), (int)((m->T + 255) / 256)));
 }
 
+// Workgroups per 64-node block of the band kernel (after the matrix-core far
+// field or the treecode; k_band takes one) for nblk blocks.  The chip holds
+// 1,792 of its workgroups (seven waves per SIMD) and blocks differ in cost,
+// so a block's tets are split until the launch has twelve rounds, four-fold at
+// least, 32-fold at most (there a wave of the smallest meshes has two or three
+// pieces left).  Band kernel alone, one workgroup per block against this: 21
+// blocks (10^3 box) 1.96 -> 0.12 ms, 313 blocks (20,011 points) 9.5 -> 2.1,
+// 1,519 (ring) 15.0 -> 10.1, 1,839 (Fourier field) 18.8 -> 13.0, 8,304 (two
+// rings) 71 -> 62 ms; beyond, the partial sums cost more than the balance
+// gains (1,519 blocks 28-fold: 10.7).
+int band_splits(const bs_mesh *m, int64_t nblk)
+{
+    const bs_policy &P = m->pol;
+    const bool fixed_like = P.kind == BS_POLICY_FIXED || P.kind == BS_POLICY_LEARNED;
+    if (!fixed_like || nblk <= 0 || !(far_on_matrix_cores(m) || uses_treecode(P))) return 1;
+    return (int)std::min<int64_t>(32, std::max<int64_t>(4, 12 * 1792 / nblk));
+}
+
 // Device buffers of one evaluation that the caller provides instead of the
 // mesh (the no-allocation entry point): partial sums, counters, the walk's
 // fallback list and the learned policy's lists, and the output.
 struct EvalBufs {
+    int nsplit; // of the band kernel
     double *part, *band, *rtv, *vel;
     unsigned long long *cnt;
     int *nonfinite, *fallback, *sel;
@@ -1843,6 +1862,8 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, const EvalBufs *given =
     if (treecode && !m->tree.valid) return fail(BS_E_STATE, "treecode plan missing (set the policy again)");
     const int splits = far_splits(m);
     if (splits > 0 && !given && (rc = dalloc(m->part, 8 * 3 * (size_t)m->npad * splits))) return rc;
+    const int nsplit = given ? given->nsplit : band_splits(m, dm.nblk);
+    if (!given && fixed_like && (rc = dalloc(m->band, 8 * 3 * (size_t)m->npad * nsplit))) return rc;
     double *b_part = given ? given->part : (double *)m->part.p;
     double *b_band = given ? given->band : (double *)m->band.p;
     double *b_rtv = given ? given->rtv : (double *)m->rtv.p;
@@ -1937,7 +1958,7 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, const EvalBufs *given =
     hipStream_t sb = one_stream ? s : m->aux[0], sr = one_stream ? s : m->aux[1];
     record(2, sb);
     if (m->T > 0 && fixed_like) {
-        if ((e = bsk::launch_band(dm, th, P.precision, (far_mfma || treecode) ? 0 : 1, b_band, cnt, sb)))
+        if ((e = bsk::launch_band(dm, th, P.precision, (far_mfma || treecode) ? 0 : 1, nsplit, b_band, cnt, sb)))
             return hip_fail(e, "band kernel");
         band = b_band;
     }
@@ -1992,7 +2013,7 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, const EvalBufs *given =
     record(6, s);
     double *out = given ? given->vel : (double *)(targets ? m->tvel.p : m->vel.p);
     if ((e = bsk::launch_combine(dm, (const int *)(targets ? m->torig.p : m->node_orig.p), part, part ? splits : 0,
-                                 band, rtv, out, b_nonfinite, s)))
+                                 band, nsplit, rtv, out, b_nonfinite, s)))
         return hip_fail(e, "combine kernel");
     record(7, s);
     if (!targets) m->vel_valid = !given;
@@ -2000,13 +2021,14 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, const EvalBufs *given =
 }
 
 // Bytes of scratch an evaluation of the nodes needs under the current
-// policy and far-field mode, laid out (256-byte aligned) as part, band, rtv,
-// counters, non-finite flag, fallback list, learned lists; offsets in off[7].
-size_t eval_scratch_layout(const bs_mesh *m, size_t off[7])
+// policy and far-field mode with nsplit band splits, laid out (256-byte
+// aligned) as part, band, rtv, counters, non-finite flag, fallback list,
+// learned lists; offsets in off[7].
+size_t eval_scratch_layout(const bs_mesh *m, int nsplit, size_t off[7])
 {
     auto al = [](size_t v) { return (v + 255) / 256 * 256; };
     const size_t np = (size_t)m->npad, nn = (size_t)m->n;
-    const size_t sz[7] = {8 * 3 * np * (size_t)far_splits(m), 8 * 3 * np, 8 * 3 * np, 8 * (size_t)bsk::kCntWords, 4,
+    const size_t sz[7] = {8 * 3 * np * (size_t)far_splits(m), 8 * 3 * np * (size_t)nsplit, 8 * 3 * np, 8 * (size_t)bsk::kCntWords, 4,
                           4 * (nn + 1),
                           m->pol.kind == BS_POLICY_LEARNED ? 4 * (nn * bsk::kSelListCap + 5 * nn) : 0};
     size_t o = 0;
@@ -2235,13 +2257,17 @@ int bs_eval_velocity_noalloc(bs_mesh *m, double *vel, uint32_t flags, void *stre
     if (!base) return fail(BS_E_DEVICE, "the static scratch of device %d is not available", m->device);
     m->far_mode = (flags & BS_EVAL_VALU_FAR) ? 1 : 0;
     size_t off[7];
-    const size_t need = eval_scratch_layout(m, off);
+    // (band splits that the scratch cannot hold are given up)
+    int nsplit = band_splits(m, m->nblk);
+    size_t need = eval_scratch_layout(m, nsplit, off);
+    if (need > bsk::kScratchBytes && nsplit > 1) need = eval_scratch_layout(m, nsplit = 1, off);
     if (need > bsk::kScratchBytes) {
         m->far_mode = 0;
         return fail(BS_E_ARG, "this mesh and policy need %zu bytes of scratch, above the static %zu", need,
                     bsk::kScratchBytes);
     }
     EvalBufs g{};
+    g.nsplit = nsplit;
     g.part = (double *)(base + off[0]);
     g.band = (double *)(base + off[1]);
     g.rtv = (double *)(base + off[2]);

@@ -21,7 +21,7 @@
 //     dir[l] = (d.xyz, kappa) binary32, dir64[l][3] FP64 directions,
 //     cphi[N] cos(polar angle) per row, dia[2M] pseudo-angle per column.
 //   outputs: part[S][3][npad] FP64 far-field partials per tet split,
-//            band[3][npad], rtv[3][npad] FP64 near partials, vel[n][3].
+//            band[splits][3][npad], rtv[3][npad] FP64 near partials, vel[n][3].
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -115,8 +115,10 @@ hipError_t launch_gauss_all(const DevMesh &m, int rule_pts, int precision, int s
 // Far field of the fixed-rule policies (G1 pairs only), precision 0 or 1.
 hipError_t launch_far_mfma(const DevMesh &m, const Thresholds &th, int precision, int splits, double *part,
                            hipStream_t s);
-// sub_g1: also remove the G1 term of non-G1 pairs (after launch_gauss_all).
-hipError_t launch_band(const DevMesh &m, const Thresholds &th, int precision, int sub_g1, double *band,
+// sub_g1: also remove the G1 term of non-G1 pairs (after launch_gauss_all;
+// nsplit must be 1).  band: [nsplit][3][npad] partial sums, a block's tets
+// split among nsplit workgroups.
+hipError_t launch_band(const DevMesh &m, const Thresholds &th, int precision, int sub_g1, int nsplit, double *band,
                        unsigned long long *cnt, hipStream_t s);
 hipError_t launch_rt(const DevMesh &m, const Thresholds &th, const AngTab &ang, const LearnParams &lp,
                      int all_pairs, int precision, double *rtv, unsigned long long *cnt, const int *node_list,
@@ -145,7 +147,8 @@ hipError_t launch_velocity_gradient(const DevMesh &m, const int *node_orig, cons
 // Vortex stretching rate rate[i] = grad[i] om[i] (input order, FP64).
 hipError_t launch_stretching(int n, const double *grad, const double *om, double *rate, hipStream_t s);
 hipError_t launch_combine(const DevMesh &m, const int *node_orig, const double *part, int splits,
-                          const double *band, const double *rtv, double *vel, int *nonfinite, hipStream_t s);
+                          const double *band, int nsplit, const double *rtv, double *vel, int *nonfinite,
+                          hipStream_t s);
 
 // Treecode far field (BS_FAR_TREECODE): the plan the host builds and the
 // per-evaluation moment buffers.  Clusters are numbered breadth first, so

@@ -1024,9 +1024,9 @@ __global__ void __launch_bounds__(64 * kBandWaves) k_band(DevMesh m, Thresholds 
     }
 }
 
-// Band pairs after k_far_mfma (no G1 terms to remove): k_band's blocks,
-// waves, rows and rule masks, but each wave streams its rows in pieces of 32
-// tets staged in its own LDS.  The centroids and G4 points of the next piece
+// Band pairs after k_far_mfma (no G1 terms to remove): k_band's blocks and
+// rule masks, but each wave takes pieces of 32 tets of the block's rows,
+// staged in its own LDS.  The centroids and G4 points of the next piece
 // are loaded into registers while the current piece is evaluated, so a tet
 // costs LDS broadcast reads instead of dependent scalar loads from L2 (the
 // G11 points, needed for few tets, stay scalar loads).  The FP32 sums of a
@@ -1042,17 +1042,23 @@ struct BandPieceLds {
 // Seven waves per SIMD (72 registers, a few spilled outside the point
 // loop): the kernel waits on its record loads and LDS reads as well as
 // issuing; at six waves it took 74.5 ms on the two-ring mesh, at seven 72.0.
+//
+// A block's pieces are dealt to the waves of nsplit workgroups, each writing
+// partial sums of its own (band[split]): one workgroup per block leaves most
+// of the chip idle on a small mesh and a long last round on a large one
+// (band_splits has the figures).
 template <int PREC>
-__global__ void __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu(7))) k_band_piece(DevMesh m, Thresholds th, double *__restrict__ band,
+__global__ void __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_per_eu(7))) k_band_piece(DevMesh m, Thresholds th, int nsplit, double *__restrict__ band,
                                                                 unsigned long long *__restrict__ cnt)
 {
     __shared__ double red[kBandWaves][3][64];
     __shared__ BandPieceLds P[kBandWaves];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int per_xcd = (m.nblk + 7) >> 3;
-    const int lb = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (lb >= m.nblk) return;
+    const int per_xcd = (m.nblk * nsplit + 7) >> 3;
+    const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (item >= m.nblk * nsplit) return;
+    const int lb = item / nsplit, split = item - lb * nsplit;
     const int blk = m.blk0 + lb;
     const int i = blk * kBlockNodes + lane;
     const bool valid = i < m.nv;
@@ -1062,7 +1068,22 @@ __global__ void __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_p
     double dx = 0.0, dy = 0.0, dz = 0.0;
     unsigned long long n4 = 0, n11 = 0;
     RowIter rows(m, bc.x, bc.y, bc.z, th.r_band + bc.w);
-    int row = 0, c0 = 0, c1 = 0, t0, t1;
+    // the pieces of all rows, numbered in order; this wave's are first,
+    // first + stride, ...
+    const int first = split * kBandWaves + wave, stride = kBandWaves * nsplit;
+    int at = 0, c0 = 0, c1 = 0, t0 = 0, t1 = 0;
+    // the next piece [c0, c1) of this wave (c1: the end of its row)
+    auto next_piece = [&]() -> bool {
+        // at: the wanted piece, counted from the current row's first
+        at += c1 > 0 ? stride : first;
+        while (at >= (t1 - t0 + kBandPiece - 1) / kBandPiece) {
+            at -= (t1 - t0 + kBandPiece - 1) / kBandPiece;
+            if (!rows.next(t0, t1)) return false;
+        }
+        c0 = t0 + at * kBandPiece;
+        c1 = t1;
+        return true;
+    };
     // lane l: tet c0 + l % 32 (clamped to the piece), G4 points 2h, 2h + 1
     // with h = l / 32; lanes below 32 also the centroid
     const int k = lane & (kBandPiece - 1), h = lane >> 5;
@@ -1078,15 +1099,7 @@ __global__ void __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_p
         ra1 = *reinterpret_cast<const float4 *>(g_ + kRecG);                                           \
         rb1 = *reinterpret_cast<const float2 *>(g_ + kRecG + 4);                                       \
     } while (0)
-    // the first piece of this wave's rows
-    bool have = false;
-    while (rows.next(t0, t1)) {
-        if ((row++ % kBandWaves) != wave) continue;
-        c0 = t0;
-        c1 = t1;
-        have = true;
-        break;
-    }
+    bool have = next_piece();
     if (have) BAND_FETCH();
     while (have) {
         const int p0 = c0, pn = min(kBandPiece, c1 - c0);
@@ -1103,19 +1116,7 @@ __global__ void __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_p
         P[wave].pa[k][2 * h] = ra0;
         P[wave].pa[k][2 * h + 1] = ra1;
         P[wave].pb[k][h] = make_float4(rb0.x, rb0.y, rb1.x, rb1.y);
-        // the next piece: the rest of this row, else this wave's next row
-        if (c0 + kBandPiece < c1) {
-            c0 += kBandPiece;
-        } else {
-            have = false;
-            while (rows.next(t0, t1)) {
-                if ((row++ % kBandWaves) != wave) continue;
-                c0 = t0;
-                c1 = t1;
-                have = true;
-                break;
-            }
-        }
+        have = next_piece();
         if (have) BAND_FETCH();
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -1195,16 +1196,17 @@ __global__ void __launch_bounds__(64 * kBandWaves) __attribute__((amdgpu_waves_p
             double v = red[0][c][lane];
 #pragma unroll
             for (int w = 1; w < kBandWaves; ++w) v += red[w][c][lane];
-            band[(size_t)c * m.npad + i] = v;
+            band[((size_t)split * 3 + c) * m.npad + i] = v;
         }
     }
 }
 
-hipError_t launch_band(const DevMesh &m, const Thresholds &th, int precision, int sub_g1, double *band,
+hipError_t launch_band(const DevMesh &m, const Thresholds &th, int precision, int sub_g1, int nsplit, double *band,
                        unsigned long long *cnt, hipStream_t s)
 {
+    if (nsplit < 1 || (sub_g1 && nsplit != 1)) return hipErrorInvalidValue;
     const dim3 blk(64 * kBandWaves);
-    const dim3 grid(8 * ((m.nblk + 7) / 8));
+    const dim3 grid(8 * ((m.nblk * nsplit + 7) / 8));
     if (sub_g1) {
         if (precision == 0)
             hipLaunchKernelGGL(k_band<0>, grid, blk, 0, s, m, th, band, cnt);
@@ -1214,11 +1216,11 @@ hipError_t launch_band(const DevMesh &m, const Thresholds &th, int precision, in
             hipLaunchKernelGGL(k_band<2>, grid, blk, 0, s, m, th, band, cnt);
     } else {
         if (precision == 0)
-            hipLaunchKernelGGL(k_band_piece<0>, grid, blk, 0, s, m, th, band, cnt);
+            hipLaunchKernelGGL(k_band_piece<0>, grid, blk, 0, s, m, th, nsplit, band, cnt);
         else if (precision == 1)
-            hipLaunchKernelGGL(k_band_piece<1>, grid, blk, 0, s, m, th, band, cnt);
+            hipLaunchKernelGGL(k_band_piece<1>, grid, blk, 0, s, m, th, nsplit, band, cnt);
         else
-            hipLaunchKernelGGL(k_band_piece<2>, grid, blk, 0, s, m, th, band, cnt);
+            hipLaunchKernelGGL(k_band_piece<2>, grid, blk, 0, s, m, th, nsplit, band, cnt);
     }
     return hipGetLastError();
 }
@@ -2623,8 +2625,9 @@ hipError_t launch_rt_walk(const DevMesh &m, const Thresholds &th, const AngTab &
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_combine(int n, int first, int npad, const int *__restrict__ node_orig,
                                                  const double *__restrict__ part, int splits,
-                                                 const double *__restrict__ band, const double *__restrict__ rtv,
-                                                 double *__restrict__ vel, int *__restrict__ nonfinite)
+                                                 const double *__restrict__ band, int nsplit,
+                                                 const double *__restrict__ rtv, double *__restrict__ vel,
+                                                 int *__restrict__ nonfinite)
 {
     const int k = blockIdx.x * 256 + threadIdx.x;
     if (k >= n) return;
@@ -2635,7 +2638,7 @@ __global__ void __launch_bounds__(256) k_combine(int n, int first, int npad, con
     for (int c = 0; c < 3; ++c) {
         double v = 0.0;
         for (int s = 0; s < splits; ++s) v += part[((size_t)s * 3 + c) * npad + i];
-        if (band) v += band[(size_t)c * npad + i];
+        for (int s = 0; band && s < nsplit; ++s) v += band[((size_t)s * 3 + c) * npad + i];
         if (rtv) v += rtv[(size_t)c * npad + i];
         vel[3 * (size_t)o + c] = v;
         bad |= !isfinite(v);
@@ -2644,11 +2647,12 @@ __global__ void __launch_bounds__(256) k_combine(int n, int first, int npad, con
 }
 
 hipError_t launch_combine(const DevMesh &m, const int *node_orig, const double *part, int splits,
-                          const double *band, const double *rtv, double *vel, int *nonfinite, hipStream_t s)
+                          const double *band, int nsplit, const double *rtv, double *vel, int *nonfinite,
+                          hipStream_t s)
 {
     if (m.n == 0) return hipSuccess;
     hipLaunchKernelGGL(k_combine, dim3((m.n + 255) / 256), dim3(256), 0, s, m.n, m.blk0 * kBlockNodes, m.npad,
-                       node_orig, part, splits, band, rtv, vel, nonfinite);
+                       node_orig, part, splits, band, nsplit, rtv, vel, nonfinite);
     return hipGetLastError();
 }
 
