@@ -203,13 +203,13 @@ typedef struct {
     int64_t tree_direct;      /* TREECODE: (node, tet) pairs of direct leaves  */
     int64_t tree_covered;     /* TREECODE: (node, tet) pairs the expansions sum */
     int64_t rt_walk_nodes;    /* nodes ray traced by walking face neighbours   */
-    int64_t rt_candidate_nodes; /* nodes ray traced by candidate rays per pair:
-                                 * off-node points, pure ray tracing on a
-                                 * boundary that is not convex, nodes with no
-                                 * or more than 48 incident tets, and, where the
+    int64_t rt_candidate_nodes; /* nodes with candidate rays tested, per pair:
+                                 * off-node points, nodes with no or more than
+                                 * 48 incident tets; or per boundary face, for
+                                 * rays entering the mesh again: where the
                                  * boundary is not convex, nodes with a ray
                                  * that leaves the mesh before its last
-                                 * ray-traced tet                              */
+                                 * ray-traced tet (pure ray tracing: all)     */
 } bs_stats;
 
 /* Velocity at every node, written to vel ([n_nodes][3] FP64, input node

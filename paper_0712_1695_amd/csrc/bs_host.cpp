@@ -314,7 +314,9 @@ struct bs_mesh {
     bsk::Bins bins{};
     // device buffers
     DBuf tsph; // bounding spheres of 16-tet tiles
-    DBuf xh, xl, om, nrec, blk, node_orig, g1, g4, g11, tid, cell_start, nbr, inc_start, inc_list;
+    DBuf xh, xl, om, nrec, blk, node_orig, g1, g4, g11, tid, cell_start, nbr, inc_start, inc_list, bface, bsph;
+    int nbface = 0;                  // boundary faces in bface (0 where the boundary is convex)
+    std::vector<int64_t> bface_in;   // 4 * tet + face of every boundary face, input numbering
     DBuf part, band, rtv, vel, cnt, nonfinite, fallback;
     // evaluation points (bs_eval_points): FP64 copy, count, first node index
     // and first block in the node arrays, their order and output
@@ -1334,6 +1336,48 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
     th_convex.join();
     m->convex = convex;
 
+    // ---- boundary faces for rays that enter the mesh again (only where they
+    // can), with a bounding sphere per 64
+    std::vector<int2> bface;
+    std::vector<float4> bsph;
+    if (m->manifold && !convex) {
+        if (m->bface_in.empty())
+            for (int64_t i = 0; i < 4 * T; ++i)
+                if (m->nbr_in[(size_t)i] < 0) m->bface_in.push_back(i);
+        bface.resize(m->bface_in.size());
+        for (size_t i = 0; i < bface.size(); ++i) {
+            // [v_p - v_f, v_q - v_f, v_r - v_f], p < q < r, has the sign of the
+            // tet's determinant for f = 0, 2 and the opposite one for f = 1, 3
+            const int64_t t = m->bface_in[i] >> 2;
+            const int f = (int)(m->bface_in[i] & 3);
+            const bool pos = (m->orient[(size_t)t] > 0) == ((f & 1) == 0);
+            bface[i] = make_int2(slot[(size_t)t], f | (pos ? 0 : 4));
+        }
+        std::sort(bface.begin(), bface.end(),
+                  [](const int2 &u, const int2 &v) { return u.x < v.x || (u.x == v.x && (u.y & 3) < (v.y & 3)); });
+        bsph.resize((bface.size() + 63) / 64);
+        for (size_t g = 0; g < bsph.size(); ++g) {
+            double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300}, r2 = 0.0;
+            const size_t a = 64 * g, b = std::min(bface.size(), a + 64);
+            auto each = [&](auto &&fn) {
+                for (size_t i = a; i < b; ++i)
+                    for (int j = 0; j < 4; ++j)
+                        if (j != (bface[i].y & 3)) fn(&X[3 * (int64_t)m->tets[4 * (int64_t)order[(size_t)bface[i].x] + j]]);
+            };
+            each([&](const double *x) {
+                for (int c = 0; c < 3; ++c) lo[c] = std::min(lo[c], x[c]), hi[c] = std::max(hi[c], x[c]);
+            });
+            const float cc[3] = {(float)(0.5 * (lo[0] + hi[0])), (float)(0.5 * (lo[1] + hi[1])), (float)(0.5 * (lo[2] + hi[2]))};
+            each([&](const double *x) {
+                double d2 = 0.0;
+                for (int c = 0; c < 3; ++c) d2 += (x[c] - cc[c]) * (x[c] - cc[c]);
+                r2 = std::max(r2, d2);
+            });
+            bsph[g] = make_float4(cc[0], cc[1], cc[2], (float)(std::sqrt(r2) * (1.0 + 1e-5) + 1e-6));
+        }
+    }
+    m->nbface = (int)bface.size();
+
     // ---- upload
     const size_t nb = sizeof(float) * 3 * (size_t)npad;
     if ((rc = dalloc(m->xh, nb)) || (rc = dalloc(m->xl, nb)) || (rc = dalloc(m->om, nb)) ||
@@ -1346,6 +1390,8 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
         (rc = dalloc(m->cnt, 8 * bsk::kCntWords)) || (rc = dalloc(m->nonfinite, 4)) ||
         (rc = dalloc(m->nbr, sizeof(int4) * (size_t)T)) ||
         (rc = dalloc(m->tsph, sizeof(float4) * tsph.size())) || (rc = dalloc(m->inc_start, 4 * inc_start.size())) ||
+        (rc = dalloc(m->bface, sizeof(int2) * std::max<size_t>(bface.size(), 1))) ||
+        (rc = dalloc(m->bsph, sizeof(float4) * std::max<size_t>(bsph.size(), 1))) ||
         (rc = dalloc(m->inc_list, 4 * inc_list.size())) || (rc = dalloc(m->om64, 8 * 3 * (size_t)std::max<int64_t>(n, 1))))
         return wait_records(rc);
     hipError_t e;
@@ -1368,6 +1414,8 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
     BS_UP(tsph, tsph)
     BS_UP(inc_start, inc_start)
     BS_UP(inc_list, inc_list)
+    BS_UP(bface, bface)
+    BS_UP(bsph, bsph)
     BS_UP(om64, m->omega)
 #undef BS_UP
     e = hipStreamSynchronize(s);
@@ -1699,7 +1747,7 @@ void bs_mesh_free(bs_mesh *m)
     if (!m) return;
     DBuf *bufs[] = {&m->xh, &m->xl, &m->om, &m->nrec, &m->tsph, &m->blk, &m->node_orig, &m->g1, &m->g4, &m->g11, &m->tid,
                     &m->nbr, &m->inc_start, &m->inc_list, &m->fallback,
-                    &m->cell_start, &m->part, &m->band, &m->rtv, &m->vel, &m->cnt, &m->nonfinite, &m->dir,
+                    &m->cell_start, &m->bface, &m->bsph, &m->part, &m->band, &m->rtv, &m->vel, &m->cnt, &m->nonfinite, &m->dir,
                     &m->dir64, &m->cphi, &m->dia, &m->mlp, &m->sel, &m->torig, &m->tlist, &m->tvel,
                     &m->gvel, &m->tgrad, &m->ngrad, &m->om64, &m->srate,
                     &m->tree.nrange, &m->tree.child, &m->tree.leaves, &m->tree.c64, &m->tree.crec,
@@ -1972,11 +2020,10 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, const EvalBufs *given =
     if (m->T > 0 && (fixed_like || P.kind == BS_POLICY_PURE_RT)) {
         const int all = P.kind == BS_POLICY_PURE_RT;
         m->last_rt = 1;
-        // the walk on face-manifold meshes; where the boundary is not
-        // convex it leaves every node with a ray that exits the mesh early
-        // to the candidate kernel (with every pair ray traced, rays run to
-        // the boundary: there every node goes to the candidate kernel)
-        if (m->manifold && (m->convex || !all) && m->rt_mode == 0 && !targets) {
+        // the walk on face-manifold meshes; where the boundary is not convex,
+        // nodes with a ray that exits the mesh early take another pass for
+        // the boundary faces through which it can enter again
+        if (m->manifold && m->rt_mode == 0 && !targets) {
             m->last_rt = 2;
             if (!given && (rc = dalloc(m->fallback, 4 * ((size_t)m->n + 1)))) return rc;
             int *fb = given ? given->fallback : (int *)m->fallback.p;
@@ -1995,9 +2042,13 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, const EvalBufs *given =
             if ((e = given ? bsk::launch_fill_zero(nfb, 1, sr) : hipMemsetAsync(nfb, 0, 4, sr)) ||
                 (lp.net && (e = bsk::launch_select(dm, th, lp, P.precision, b_rtv, sel_list, sel_n, sel_dmax,
                                                    sel_cnt, sr))) ||
-                (e = bsk::launch_rt_walk(dm, th, ang, all, r_stop, m->convex ? 0 : 1, P.precision, b_rtv, cnt, fb,
-                                         nfb, sel_list, sel_n, sel_dmax, sel_cnt, sr)) ||
-                (e = bsk::launch_rt(dm, th, ang, lp, all, P.precision, b_rtv, cnt, fb, nfb, sr)))
+                (e = bsk::launch_rt_walk(dm, th, ang, all, r_stop, m->convex ? nullptr : cnt + 8, P.precision, b_rtv, cnt,
+                                         fb, nfb, sel_list, sel_n, sel_dmax, sel_cnt, sr)) ||
+                (e = bsk::launch_rt(dm, th, ang, lp, all, P.precision, b_rtv, cnt, fb, nfb, sr)) ||
+                (!m->convex && (e = bsk::launch_rt_reenter(dm, th, ang,
+                                                           {(const int2 *)m->bface.p, (const float4 *)m->bsph.p, m->nbface},
+                                                           all, r_stop, P.precision, b_rtv, cnt, fb, cnt + 8, sel_list,
+                                                           sel_n, sr))))
                 return hip_fail(e, "ray-tracing walk");
         } else if ((e = bsk::launch_rt(dm, th, ang, lp, all, P.precision, b_rtv, cnt,
                                        targets ? (const int *)m->tlist.p : nullptr,
@@ -2084,6 +2135,7 @@ int read_stats(bs_mesh *m, bs_stats *st)
         int nfb = 0;
         if ((e = hipMemcpy(&nfb, (const int *)m->fallback.p + m->n, 4, hipMemcpyDeviceToHost)))
             return hip_fail(e, "read counters");
+        nfb += (int)cc[8]; // nodes with rays that leave the mesh early
         st->rt_candidate_nodes = nfb;
         st->rt_walk_nodes = nt - nfb;
     } else if (m->last_rt == 1) {

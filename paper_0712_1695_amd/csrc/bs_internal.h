@@ -100,6 +100,7 @@ struct DevMesh {
 // Counters accumulated by the kernels (device, 64-bit):
 // [0] G4 pairs, [1] G11 pairs, [2] RT pairs, [3] RT hit lines, [4] FP64 retests,
 // [5..7] pairs the learned selector moved from RT to G1 / G4 / G11.
+// [8] of the first copy: nodes listed for launch_rt_reenter.
 // Kept in kCntStripes copies, one 128-byte cache line each, a node or block
 // adding to copy (its index mod kCntStripes): atomics of every node on one
 // line serialise in the L2 and bound the per-node kernels.  The host sums
@@ -130,15 +131,32 @@ constexpr int kSelListCap = 128;
 hipError_t launch_select(const DevMesh &m, const Thresholds &th, const LearnParams &lp, int precision, double *rtv,
                          int *sel_list, int *sel_n, float *sel_dmax, int *sel_cnt, hipStream_t s);
 // Walk variant (face-manifold meshes); nodes it cannot hold are appended to
-// fallback[*n_fallback] for launch_rt in node-list mode: with exit_fb (a
-// boundary that is not convex) also every node with a ray that leaves the
-// mesh before its stop distance.  With sel_n the ray-traced tets come from
-// launch_select, the walk adds to rtv and, for the nodes it completes, adds
-// sel_cnt[3 node + k] (pairs moved to G1, G4, G11) to the counters.
+// fallback[*n_fallback] for launch_rt in node-list mode.  With n_reenter (a
+// boundary that is not convex) nodes with a ray that leaves the mesh before
+// its stop distance are listed from the back of the same array
+// (fallback[n - 1 - k], k < *n_reenter) for launch_rt_reenter, which adds what
+// their rays meet after entering the mesh again.  With sel_n the ray-traced
+// tets come from launch_select, the walk adds to rtv and, for the nodes it
+// completes, adds sel_cnt[3 node + k] (pairs moved to G1, G4, G11) to the
+// counters.
 hipError_t launch_rt_walk(const DevMesh &m, const Thresholds &th, const AngTab &ang, int all_pairs, float r_stop,
-                          int exit_fb, int precision, double *rtv, unsigned long long *cnt, int *fallback,
-                          int *n_fallback, const int *sel_list, const int *sel_n, const float *sel_dmax,
-                          const int *sel_cnt, hipStream_t s);
+                          unsigned long long *n_reenter, int precision, double *rtv, unsigned long long *cnt,
+                          int *fallback, int *n_fallback, const int *sel_list, const int *sel_n,
+                          const float *sel_dmax, const int *sel_cnt, hipStream_t s);
+// The boundary faces of the mesh, for rays that enter it from outside:
+// face[k] = (tet, f | 4 o): the face opposite the tet's vertex f, with p < q <
+// r its vertices in local order; o = 0 if [p - x, q - x, r - x] is positive
+// for a point x on the tet's side of it.  Groups of 64 with a bounding sphere
+// each.
+struct BoundaryFaces {
+    const int2 *face;
+    const float4 *sph; // [ceil(n / 64)]
+    int n;
+};
+hipError_t launch_rt_reenter(const DevMesh &m, const Thresholds &th, const AngTab &ang, const BoundaryFaces &bf,
+                             int all_pairs, float r_stop, int precision, double *rtv, unsigned long long *cnt,
+                             const int *list, const unsigned long long *count, const int *sel_list, const int *sel_n,
+                             hipStream_t s);
 // Nodal velocity gradient (grad[input node][3][3], FP64) of the linear
 // interpolant of vel ([input node][3]) on each tet, volume-weighted over the
 // node's tets; tg: scratch of 10 doubles per tet.

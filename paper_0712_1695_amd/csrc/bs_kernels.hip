@@ -1314,6 +1314,54 @@ __device__ __forceinline__ void cross_canon(const float *A, const float *B, floa
     N[2] = fmaf(A[0], B[1], -(A[1] * B[0]));
 }
 
+// Rectangle of ray indices (rows r0 .. r0 + nr - 1, columns c0 .. c0 + nc - 1,
+// wrapping) that covers the cone of half angle acos(cosa) around the unit
+// vector U (cosa < -1.5: every ray).
+__device__ __forceinline__ void ray_rect(const AngTab &ang, const float *U, float cosa, int &r0, int &nr, int &c0,
+                                         int &nc)
+{
+    r0 = 0, nr = ang.N, c0 = 0, nc = ang.M2;
+    if (cosa > -1.5f) {
+        const float sina = sqrtf(fmaxf(0.f, 1.f - cosa * cosa));
+        const float rxy = sqrtf(fmaxf(0.f, 1.f - U[2] * U[2]));
+        const bool north = U[2] >= cosa, south = -U[2] >= cosa;
+        const float chi = north ? 2.f : fmaf(U[2], cosa, rxy * sina) + 1e-5f;
+        const float clo = south ? -2.f : fmaf(U[2], cosa, -rxy * sina) - 1e-5f;
+        // rows: cphi descending; rows n with clo <= cphi[n] <= chi
+        int lo = 0, hi = ang.N;
+        while (lo < hi) { // first n with cphi[n] <= chi
+            const int mid = (lo + hi) >> 1;
+            if (ang.cphi[mid] > chi) lo = mid + 1;
+            else hi = mid;
+        }
+        r0 = lo;
+        lo = r0;
+        hi = ang.N;
+        while (lo < hi) { // first n with cphi[n] < clo
+            const int mid = (lo + hi) >> 1;
+            if (ang.cphi[mid] >= clo) lo = mid + 1;
+            else hi = mid;
+        }
+        nr = lo - r0;
+        if (!(north || south) && rxy > 0.f && sina < rxy) {
+            const float sb = sina / rxy;
+            const float cb = sqrtf(fmaxf(0.f, 1.f - sb * sb));
+            const float ct = U[0] / rxy, st = U[1] / rxy;
+            // endpoints at azimuth theta_U -+ beta
+            const float dlo0 = diamond(fmaf(ct, cb, st * sb), fmaf(st, cb, -ct * sb)) - 2e-4f;
+            const float dhi0 = diamond(fmaf(ct, cb, -st * sb), fmaf(st, cb, ct * sb)) + 2e-4f;
+            const float dlo = dlo0 < 0.f ? dlo0 + 4.f : dlo0;
+            const float dhi = dhi0 >= 4.f ? dhi0 - 4.f : dhi0;
+            const int jlo = lower_bound_f(ang.dia, ang.M2, dlo); // first column with dia >= dlo
+            const int jhi = upper_bound_f(ang.dia, ang.M2, dhi) - 1; // last column with dia <= dhi
+            c0 = jlo;
+            if (dlo <= dhi) nc = max(0, jhi - jlo + 1);
+            else nc = min(ang.M2, (ang.M2 - jlo) + (jhi + 1));
+            if (c0 >= ang.M2) c0 -= ang.M2;
+        }
+    }
+}
+
 // Pair setup for lane p (tet t, node self at (xh, xl)).  Returns the number
 // of candidate rays.
 __device__ int rt_setup(const DevMesh &m, const AngTab &ang, RtLds &L, int p, int t, int self, const float *xhv,
@@ -1388,47 +1436,8 @@ __device__ int rt_setup(const DevMesh &m, const AngTab &ang, RtLds &L, int p, in
     L.cone[2][p] = U[2];
     L.cone[3][p] = cull ? cosa : -2.f;
 
-    // rectangle of ray indices covering the cone
-    int r0 = 0, nr = ang.N, c0 = 0, nc = ang.M2;
-    if (cull) {
-        const float sina = sqrtf(fmaxf(0.f, 1.f - cosa * cosa));
-        const float rxy = sqrtf(fmaxf(0.f, 1.f - U[2] * U[2]));
-        const bool north = U[2] >= cosa, south = -U[2] >= cosa;
-        const float chi = north ? 2.f : fmaf(U[2], cosa, rxy * sina) + 1e-5f;
-        const float clo = south ? -2.f : fmaf(U[2], cosa, -rxy * sina) - 1e-5f;
-        // rows: cphi descending; rows n with clo <= cphi[n] <= chi
-        int lo = 0, hi = ang.N;
-        while (lo < hi) { // first n with cphi[n] <= chi
-            const int mid = (lo + hi) >> 1;
-            if (ang.cphi[mid] > chi) lo = mid + 1;
-            else hi = mid;
-        }
-        r0 = lo;
-        lo = r0;
-        hi = ang.N;
-        while (lo < hi) { // first n with cphi[n] < clo
-            const int mid = (lo + hi) >> 1;
-            if (ang.cphi[mid] >= clo) lo = mid + 1;
-            else hi = mid;
-        }
-        nr = lo - r0;
-        if (!(north || south) && rxy > 0.f && sina < rxy) {
-            const float sb = sina / rxy;
-            const float cb = sqrtf(fmaxf(0.f, 1.f - sb * sb));
-            const float ct = U[0] / rxy, st = U[1] / rxy;
-            // endpoints at azimuth theta_U -+ beta
-            const float dlo0 = diamond(fmaf(ct, cb, st * sb), fmaf(st, cb, -ct * sb)) - 2e-4f;
-            const float dhi0 = diamond(fmaf(ct, cb, -st * sb), fmaf(st, cb, ct * sb)) + 2e-4f;
-            const float dlo = dlo0 < 0.f ? dlo0 + 4.f : dlo0;
-            const float dhi = dhi0 >= 4.f ? dhi0 - 4.f : dhi0;
-            const int jlo = lower_bound_f(ang.dia, ang.M2, dlo); // first column with dia >= dlo
-            const int jhi = upper_bound_f(ang.dia, ang.M2, dhi) - 1; // last column with dia <= dhi
-            c0 = jlo;
-            if (dlo <= dhi) nc = max(0, jhi - jlo + 1);
-            else nc = min(ang.M2, (ang.M2 - jlo) + (jhi + 1));
-            if (c0 >= ang.M2) c0 -= ang.M2;
-        }
-    }
+    int r0, nr, c0, nc;
+    ray_rect(ang, U, cull ? cosa : -2.f, r0, nr, c0, nc);
     L.rows[p] = r0;
     L.cols[p] = c0;
     L.ncol[p] = nc;
@@ -1911,7 +1920,7 @@ __global__ void __launch_bounds__(64) k_rt(DevMesh m, Thresholds th, AngTab ang,
 // Ray tracing by walking the mesh (face-manifold meshes: every interior
 // face shared by two tets).  Where the boundary is not convex a ray that
 // leaves the mesh may enter it again, so a node with a ray that leaves
-// before its stop distance (or starts outside) is left to k_rt.
+// before its stop distance (or starts outside) is listed for k_rt_reenter.
 // One wave per node; lane = ray.  Every ray leaves the node through the one
 // incident tet whose opposite face it crosses, then crosses face neighbours
 // outward: the exit face of one tet is the entry face of the next, decided
@@ -2128,13 +2137,159 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) k_
     }
 }
 
+// Walks a ray that enters tet T at distance rho through the face e (nodes)
+// with relative positions P, vorticity Wv, edge values cf (all of sign sg)
+// and vorticity w_in at the crossing, until it leaves the mesh (T < 0) or is
+// past stop_r.  Chords of ray-traced tets go to ray (compensated mode) or A.
+template <int PREC, bool LISTED>
+__device__ __forceinline__ void walk_ray(const DevMesh &m, const Thresholds &th, int all_pairs, const float4 &d,
+                                         const double *d64, const float *xhv, const float *xlv, const int *list,
+                                         int nlist, float stop_r, int sg, int &T, const int (&e0)[3],
+                                         const float (&P0)[3][3], const float (&Wv0)[3][3], const float (&cf0)[3],
+                                         const float (&w0)[3], float &rho, float (&ray)[3], RtAcc &A)
+{
+    // local copies: the compiler keeps these in registers, where selects
+    // between elements of an argument array become indexed scratch loads
+    int e[3];
+    float P[3][3], Wv[3][3], cf[3], w_in[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        e[q] = e0[q];
+        cf[q] = cf0[q];
+        w_in[q] = w0[q];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            P[q][c] = P0[q][c];
+            Wv[q][c] = Wv0[q][c];
+        }
+    }
+    int steps = 0;
+    while (T >= 0 && rho < stop_r && steps < kMaxSteps) {
+        ++steps;
+        const int4 id4 = m.tid[T];
+        const int4 nb4 = m.nbr[T];
+        float4 cen = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (!all_pairs) cen = *reinterpret_cast<const float4 *>(m.g1 + (size_t)T * kRecG);
+        // the node of T off the entry face
+        const int v = (id4.x ^ id4.y ^ id4.z ^ id4.w) ^ (e[0] ^ e[1] ^ e[2]);
+        const float4 r0 = m.nrec[2 * v], r1 = m.nrec[2 * v + 1];
+        const float wz = m.om[2 * m.npad + v];
+        const float av[3] = {(r0.x - xhv[0]) + (r0.w - xlv[0]), (r0.y - xhv[1]) + (r1.x - xlv[1]),
+                             (r0.z - xhv[2]) + (r1.y - xlv[2])};
+        const float wv[3] = {r1.z, r1.w, wz};
+        float cv[3];
+        int sv[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) cv[k] = edge_val(d, av, v, P[k], e[k], m, d64, xhv, xlv, sv[k], A.retests);
+        const bool x0 = sv[0] == sg && sv[1] != sg;
+        const bool x1 = sv[1] == sg && sv[2] != sg;
+        const bool x2 = sv[2] == sg && sv[0] != sg;
+        if (!(x0 || x1 || x2)) break; // the ray meets V: end it here
+        // exit face (V, A, B) = (V, P_k, P_k+1); O = P_k+2 is the node of T off it
+        float pa[3], pb[3], wa[3], wb[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            pa[c] = x0 ? P[0][c] : (x1 ? P[1][c] : P[2][c]);
+            pb[c] = x0 ? P[1][c] : (x1 ? P[2][c] : P[0][c]);
+            wa[c] = x0 ? Wv[0][c] : (x1 ? Wv[1][c] : Wv[2][c]);
+            wb[c] = x0 ? Wv[1][c] : (x1 ? Wv[2][c] : Wv[0][c]);
+        }
+        const int ea = x0 ? e[0] : (x1 ? e[1] : e[2]);
+        const int eb = x0 ? e[1] : (x1 ? e[2] : e[0]);
+        const int eo = x0 ? e[2] : (x1 ? e[0] : e[1]);
+        const float cVA = x0 ? cv[0] : (x1 ? cv[1] : cv[2]);
+        const float cAB = x0 ? cf[0] : (x1 ? cf[1] : cf[2]);
+        const float cBV = -(x0 ? cv[1] : (x1 ? cv[2] : cv[0]));
+        const float Sm = (cVA + cAB) + cBV;
+        float N[3];
+        cross_canon(pa, pb, N);
+        const float vol = fmaf(av[0], N[0], fmaf(av[1], N[1], av[2] * N[2]));
+        const float inv = __builtin_amdgcn_rcpf(Sm);
+        const float rout = vol * inv;
+        if (!(rout < 3.0e38f) || !(rout > -3.0e38f)) break; // degenerate face: end the ray
+        const float lv = cAB * inv, la = cBV * inv, lb = cVA * inv;
+        float wout[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) wout[c] = fmaf(lv, wv[c], fmaf(la, wa[c], lb * wb[c]));
+        const float r_out = fmaxf(rout, rho);
+        // the fixed rule's test: past its first segment a ray meets no tet
+        // incident to the node (such a tet lies in its own cone from the
+        // node), so only the distance comparison remains; the selector's
+        // list holds only pairs the fixed rule ray-traces
+        bool take = true;
+        if (!all_pairs) {
+            const float ex = xhv[0] - cen.x, ey = xhv[1] - cen.y, ez = xhv[2] - cen.z;
+            const float qx = ex * ex, qy = ey * ey, qz = ez * ez;
+            take = (qx + qy) + qz < th.rt2;
+            if constexpr (LISTED) take = take && in_sorted(list, nlist, T);
+        }
+        if (take) {
+            const float h = 0.5f * d.w * (r_out - rho);
+            const float sx = w_in[0] + wout[0], sy = w_in[1] + wout[1], sz = w_in[2] + wout[2];
+            const float a0 = h * fmaf(d.y, sz, -(d.z * sy)), a1 = h * fmaf(d.z, sx, -(d.x * sz)),
+                        a2 = h * fmaf(d.x, sy, -(d.y * sx));
+            if (PREC == 1) {
+                ray[0] += a0;
+                ray[1] += a1;
+                ray[2] += a2;
+            } else {
+                acc_add<PREC>(A, a0, a1, a2);
+            }
+            ++A.hits;
+        }
+        // across the exit face: the face of T opposite O
+        T = id4.x == eo ? nb4.x : (id4.y == eo ? nb4.y : (id4.z == eo ? nb4.z : nb4.w));
+        rho = r_out;
+        e[0] = v;
+        e[1] = ea;
+        e[2] = eb;
+        cf[0] = cVA;
+        cf[1] = cAB;
+        cf[2] = cBV;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            P[0][c] = av[c];
+            P[1][c] = pa[c];
+            P[2][c] = pb[c];
+            Wv[0][c] = wv[c];
+            Wv[1][c] = wa[c];
+            Wv[2][c] = wb[c];
+            w_in[c] = wout[c];
+        }
+    }
+}
+
+// Sorts list[0 .. n) (n <= kSelListCap) in LDS, by one wave (bitonic, padded
+// with INT_MAX).
+__device__ __forceinline__ void sort_list(int *list, int n, int lane)
+{
+    int np2 = 1;
+    while (np2 < n) np2 <<= 1;
+    for (int k = n + lane; k < np2; k += 64) list[k] = 0x7fffffff;
+    __syncthreads();
+    for (int size = 2; size <= np2; size <<= 1)
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+            for (int k = lane; k < np2 / 2; k += 64) {
+                const int i = 2 * k - (k & (stride - 1));
+                const int j = i + stride;
+                const bool up = (i & size) == 0;
+                const int a = list[i], b = list[j];
+                if ((a > b) == up) {
+                    list[i] = b;
+                    list[j] = a;
+                }
+            }
+            __syncthreads();
+        }
+}
+
 // LISTED: the ray-traced tets of every node come from k_select (which also
 // wrote the node's Gauss terms to rtv: the walk adds to them).
 template <int PREC, bool LISTED>
 __global__ void __launch_bounds__(64) k_rt_walk(DevMesh m, Thresholds th, AngTab ang, int all_pairs, float r_stop,
-                                                int exit_fb, double *__restrict__ rtv,
-                                                unsigned long long *__restrict__ cnt, int *__restrict__ fallback,
-                                                int *__restrict__ n_fallback, const int *__restrict__ sel_list,
+                                                unsigned long long *__restrict__ n_reenter,
+                                                double *__restrict__ rtv, unsigned long long *__restrict__ cnt,
+                                                int *__restrict__ fallback, int *__restrict__ n_fallback, const int *__restrict__ sel_list,
                                                 const int *__restrict__ sel_n, const float *__restrict__ sel_dmax,
                                                 const int *__restrict__ sel_cnt)
 {
@@ -2186,25 +2341,7 @@ __global__ void __launch_bounds__(64) k_rt_walk(DevMesh m, Thresholds th, AngTab
                 n_lc += __popcll(mk);
             }
             dmax = sel_dmax[self];
-            // sort the list (bitonic, padded with INT_MAX)
-            int np2 = 1;
-            while (np2 < nlist) np2 <<= 1;
-            for (int k = nlist + lane; k < np2; k += 64) W.list[k] = 0x7fffffff;
-            __syncthreads();
-            for (int size = 2; size <= np2; size <<= 1)
-                for (int stride = size >> 1; stride > 0; stride >>= 1) {
-                    for (int k = lane; k < np2 / 2; k += 64) {
-                        const int i = 2 * k - (k & (stride - 1));
-                        const int j = i + stride;
-                        const bool up = (i & size) == 0;
-                        const int a = W.list[i], b = W.list[j];
-                        if ((a > b) == up) {
-                            W.list[i] = b;
-                            W.list[j] = a;
-                        }
-                    }
-                    __syncthreads();
-                }
+            sort_list(W.list, nlist, lane);
         } else {
             // chunks of 64 tets of a bin row, the next chunk's ids and
             // centroids loaded while the current one is tested
@@ -2320,16 +2457,11 @@ __global__ void __launch_bounds__(64) k_rt_walk(DevMesh m, Thresholds th, AngTab
     // ---- C. rays, 8 x 8 blocks of (row, column) per step so that the rays
     // of the wave point into a small solid angle
     const int bcols = (ang.M2 + 7) >> 3, nblk = ((ang.N + 7) >> 3) * bcols;
-    // exit_fb (a mesh whose boundary is not convex): a ray that leaves the
-    // mesh before its stop distance (or never enters it) could enter it again
-    // beyond; the node is then left to the candidate kernel, which finds
-    // every tet a ray meets
+    // n_reenter (a mesh whose boundary is not convex): a ray that leaves the
+    // mesh before its stop distance (or starts outside) could enter it again
+    // beyond; k_rt_reenter adds those parts of the node's rays
     bool early = false;
     for (int bi = 0; bi < nblk; ++bi) {
-        if (exit_fb && __ballot(early)) {
-            if (lane == 0) fallback[atomicAdd(n_fallback, 1)] = self;
-            return;
-        }
         const int row = 8 * (bi / bcols) + (lane >> 3), col = 8 * (bi % bcols) + (lane & 7);
         const bool valid = row < ang.N && col < ang.M2;
         const int l = valid ? row * ang.M2 + col : 0;
@@ -2425,107 +2557,12 @@ __global__ void __launch_bounds__(64) k_rt_walk(DevMesh m, Thresholds th, AngTab
         // compensated mode: the chords of one ray summed in FP32, the ray's
         // sum added to the node's compensated sum
         float ray[3] = {0.f, 0.f, 0.f};
-        int steps = 0;
-        while (T >= 0 && rho < stop_r && steps < kMaxSteps) {
-            ++steps;
-            const int4 id4 = m.tid[T];
-            const int4 nb4 = m.nbr[T];
-            float4 cen = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (!all_pairs) cen = *reinterpret_cast<const float4 *>(m.g1 + (size_t)T * kRecG);
-            // the node of T off the entry face
-            const int v = (id4.x ^ id4.y ^ id4.z ^ id4.w) ^ (e[0] ^ e[1] ^ e[2]);
-            const float4 r0 = m.nrec[2 * v], r1 = m.nrec[2 * v + 1];
-            const float wz = m.om[2 * m.npad + v];
-            const float av[3] = {(r0.x - xhv[0]) + (r0.w - xlv[0]), (r0.y - xhv[1]) + (r1.x - xlv[1]),
-                                 (r0.z - xhv[2]) + (r1.y - xlv[2])};
-            const float wv[3] = {r1.z, r1.w, wz};
-            float cv[3];
-            int sv[3];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) cv[k] = edge_val(d, av, v, P[k], e[k], m, d64, xhv, xlv, sv[k], A.retests);
-            const bool x0 = sv[0] == sg && sv[1] != sg;
-            const bool x1 = sv[1] == sg && sv[2] != sg;
-            const bool x2 = sv[2] == sg && sv[0] != sg;
-            if (!(x0 || x1 || x2)) break; // the ray meets V: end it here
-            // exit face (V, A, B) = (V, P_k, P_k+1); O = P_k+2 is the node of T off it
-            float pa[3], pb[3], wa[3], wb[3];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                pa[c] = x0 ? P[0][c] : (x1 ? P[1][c] : P[2][c]);
-                pb[c] = x0 ? P[1][c] : (x1 ? P[2][c] : P[0][c]);
-                wa[c] = x0 ? Wv[0][c] : (x1 ? Wv[1][c] : Wv[2][c]);
-                wb[c] = x0 ? Wv[1][c] : (x1 ? Wv[2][c] : Wv[0][c]);
-            }
-            const int ea = x0 ? e[0] : (x1 ? e[1] : e[2]);
-            const int eb = x0 ? e[1] : (x1 ? e[2] : e[0]);
-            const int eo = x0 ? e[2] : (x1 ? e[0] : e[1]);
-            const float cVA = x0 ? cv[0] : (x1 ? cv[1] : cv[2]);
-            const float cAB = x0 ? cf[0] : (x1 ? cf[1] : cf[2]);
-            const float cBV = -(x0 ? cv[1] : (x1 ? cv[2] : cv[0]));
-            const float Sm = (cVA + cAB) + cBV;
-            float N[3];
-            cross_canon(pa, pb, N);
-            const float vol = fmaf(av[0], N[0], fmaf(av[1], N[1], av[2] * N[2]));
-            const float inv = __builtin_amdgcn_rcpf(Sm);
-            const float rout = vol * inv;
-            if (!(rout < 3.0e38f) || !(rout > -3.0e38f)) break; // degenerate face: end the ray
-            const float lv = cAB * inv, la = cBV * inv, lb = cVA * inv;
-            float wout[3];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) wout[c] = fmaf(lv, wv[c], fmaf(la, wa[c], lb * wb[c]));
-            const float r_out = fmaxf(rout, rho);
-            // the fixed rule's test: past its first segment a ray meets no tet
-            // incident to the node (such a tet lies in its own cone from the
-            // node), so only the distance comparison remains; the selector's
-            // list holds only pairs the fixed rule ray-traces
-            bool take = true;
-            if (!all_pairs) {
-                const float ex = xhv[0] - cen.x, ey = xhv[1] - cen.y, ez = xhv[2] - cen.z;
-                const float qx = ex * ex, qy = ey * ey, qz = ez * ez;
-                take = (qx + qy) + qz < th.rt2;
-                if constexpr (LISTED) take = take && in_sorted(W.list, nlist, T);
-            }
-            if (take) {
-                const float h = 0.5f * d.w * (r_out - rho);
-                const float sx = w_in[0] + wout[0], sy = w_in[1] + wout[1], sz = w_in[2] + wout[2];
-                const float a0 = h * fmaf(d.y, sz, -(d.z * sy)), a1 = h * fmaf(d.z, sx, -(d.x * sz)),
-                            a2 = h * fmaf(d.x, sy, -(d.y * sx));
-                if (PREC == 1) {
-                    ray[0] += a0;
-                    ray[1] += a1;
-                    ray[2] += a2;
-                } else {
-                    acc_add<PREC>(A, a0, a1, a2);
-                }
-                ++A.hits;
-            }
-            // across the exit face: the face of T opposite O
-            T = id4.x == eo ? nb4.x : (id4.y == eo ? nb4.y : (id4.z == eo ? nb4.z : nb4.w));
-            rho = r_out;
-            e[0] = v;
-            e[1] = ea;
-            e[2] = eb;
-            cf[0] = cVA;
-            cf[1] = cAB;
-            cf[2] = cBV;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                P[0][c] = av[c];
-                P[1][c] = pa[c];
-                P[2][c] = pb[c];
-                Wv[0][c] = wv[c];
-                Wv[1][c] = wa[c];
-                Wv[2][c] = wb[c];
-                w_in[c] = wout[c];
-            }
-        }
+        walk_ray<PREC, LISTED>(m, th, all_pairs, d, d64, xhv, xlv, W.list, nlist, stop_r, sg, T, e, P, Wv, cf, w_in, rho,
+                               ray, A);
         if (PREC == 1) acc_add<1>(A, ray[0], ray[1], ray[2]);
         early = early || (T < 0 && rho < stop_r);
     }
-    if (exit_fb && __ballot(early)) {
-        if (lane == 0) fallback[atomicAdd(n_fallback, 1)] = self;
-        return;
-    }
+    if (n_reenter && __ballot(early) && lane == 0) fallback[m.n - 1 - (int)atomicAdd(n_reenter, 1ull)] = self;
     A.pairs = all_pairs ? (unsigned long long)m.T : (unsigned long long)nlist;
 
     double vx, vy, vz;
@@ -2567,6 +2604,309 @@ __global__ void __launch_bounds__(64) k_rt_walk(DevMesh m, Thresholds th, AngTab
     }
 }
 
+// ---------------------------------------------------------------------------
+// Where the boundary is not convex, a ray that has left the mesh can enter it
+// again.  The walk covers each ray from the node to where it first leaves
+// (nothing, for a ray that starts outside); every later part of the ray
+// begins where it crosses a boundary face from outside, so the parts are
+// found from the boundary alone: one wave per listed node takes the faces
+// whose outer side the node is on (on a nearly convex boundary few), tests
+// the rays of each face's cone, and walks from every crossing as k_rt_walk
+// does.  Crossings are decided by the same canonical edge signs as the
+// walk's, so a ray is never counted as entering without leaving.
+//
+// k_rt, which tests every ray-traced tet against its candidate rays, takes
+// about 3,200 vector instructions per 64 pairs; the walk 170 per crossing.
+// Ray tracing alone: every pair of a ball of 48,000 tets (9,261 nodes, 1,152
+// rays) 59.2 ms by k_rt, 3.1 so; a moved two-ring box (39,168 nodes, fixed
+// rule, 23,185 of them listed) 10.6 and 3.2 ms.
+struct EntryLds {
+    int list[kSelListCap]; // learned policy: its ray-traced tets, sorted
+    int cand[128];         // boundary faces waiting for a batch
+    float a[9][64];        // relative positions of the face's vertices p, q, r
+    float w[9][64];        // vorticity
+    float n[9][64];        // canonical normals of the edges pq, qr, pr
+    float cone[4][64];     // cone around the face: unit axis, cos(half angle) (-2: none)
+    float vol[64];         // [a_p, a_q, a_r]
+    int id[3][64];
+    int meta[64];          // bits 0-2: flip of pq, qr, pr
+    int tet[64];
+    int rows[64], cols[64], ncol[64], pref[64]; // candidate rays, as in RtLds
+};
+
+// Crossing of the face in slot p by ray l (direction d): the edge values and
+// their common sign; 0 if the ray misses the face.
+__device__ __forceinline__ int entry_cross(const DevMesh &m, const EntryLds &L, int p, const float4 &d,
+                                           const double *d64, const float *xhv, const float *xlv, float (&cf)[3],
+                                           int &retests)
+{
+    const int meta = L.meta[p];
+    int se[3];
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+        const float nx = L.n[3 * e][p], ny = L.n[3 * e + 1][p], nz = L.n[3 * e + 2][p];
+        const float c = fmaf(d.x, nx, fmaf(d.y, ny, d.z * nz));
+        int sg = c >= 0.f ? 1 : -1;
+        const bool fl = (meta >> e) & 1;
+        if (fabsf(c) <= 1e-5f * (fabsf(nx) + fabsf(ny) + fabsf(nz))) {
+            const int ep0[3] = {0, 1, 0}, ep1[3] = {1, 2, 2};
+            const int u0 = L.id[ep0[e]][p], u1 = L.id[ep1[e]][p];
+            sg = edge_sign_f64(m, d64, fl ? u1 : u0, fl ? u0 : u1, xhv, xlv);
+            ++retests;
+        }
+        se[e] = fl ? -sg : sg;
+        cf[e] = fl ? -c : c;
+    }
+    // face (p, q, r): [d,p,q] = ce0, [d,q,r] = ce1, [d,r,p] = -ce2
+    if (se[0] != se[1] || se[1] != -se[2]) return 0;
+    cf[2] = -cf[2];
+    return se[0];
+}
+
+// One batch of n <= 64 boundary faces cand[0 .. n), all with the node on
+// their outer side.
+template <int PREC, bool LISTED>
+__device__ __forceinline__ void entry_batch(const DevMesh &m, const Thresholds &th, const AngTab &ang,
+                                            const BoundaryFaces &bf, EntryLds &L, int n, int nlist, int all_pairs,
+                                            float stop, int lane, const float *xhv, const float *xlv, RtAcc &A)
+{
+    int items = 0;
+    if (lane < n) {
+        const int2 bk = bf.face[L.cand[lane]];
+        const int f = bk.y & 3;
+        const int4 id4 = m.tid[bk.x];
+        const int id[4] = {id4.x, id4.y, id4.z, id4.w};
+        int v[3], k = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (j != f) v[k++] = id[j];
+        float a[3][3], u[3][3], U[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const float4 r0 = m.nrec[2 * v[j]], r1 = m.nrec[2 * v[j] + 1];
+            a[j][0] = (r0.x - xhv[0]) + (r0.w - xlv[0]);
+            a[j][1] = (r0.y - xhv[1]) + (r1.x - xlv[1]);
+            a[j][2] = (r0.z - xhv[2]) + (r1.y - xlv[2]);
+            L.id[j][lane] = v[j];
+            L.w[3 * j][lane] = r1.z;
+            L.w[3 * j + 1][lane] = r1.w;
+            L.w[3 * j + 2][lane] = m.om[2 * m.npad + v[j]];
+            const float s = __builtin_amdgcn_rsqf(fmaf(a[j][0], a[j][0], fmaf(a[j][1], a[j][1], a[j][2] * a[j][2])));
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                L.a[3 * j + c][lane] = a[j][c];
+                u[j][c] = a[j][c] * s;
+                U[c] += u[j][c];
+            }
+        }
+        const int ep[3][2] = {{0, 1}, {1, 2}, {0, 2}};
+        int flips = 0;
+        float N[3];
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            const int x0 = ep[e][0], x1 = ep[e][1];
+            if (v[x0] < v[x1]) cross_canon(a[x0], a[x1], N);
+            else {
+                cross_canon(a[x1], a[x0], N);
+                flips |= 1 << e;
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) L.n[3 * e + c][lane] = N[c];
+        }
+        cross_canon(a[1], a[2], N);
+        L.vol[lane] = fmaf(a[0][0], N[0], fmaf(a[0][1], N[1], a[0][2] * N[2]));
+        L.meta[lane] = flips;
+        L.tet[lane] = bk.x;
+        // a cap narrower than a hemisphere that holds the face's corners
+        // holds every direction that crosses it
+        const float uu = fmaf(U[0], U[0], fmaf(U[1], U[1], U[2] * U[2]));
+        float cosa = -2.f;
+        if (uu > 0.f) {
+            const float s = __builtin_amdgcn_rsqf(uu);
+            cosa = 2.f;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) U[c] *= s;
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                cosa = fminf(cosa, fmaf(U[0], u[j][0], fmaf(U[1], u[j][1], U[2] * u[j][2])));
+            cosa = cosa - 1e-5f > 0.02f ? cosa - 1e-5f : -2.f;
+        }
+        L.cone[0][lane] = U[0];
+        L.cone[1][lane] = U[1];
+        L.cone[2][lane] = U[2];
+        L.cone[3][lane] = cosa;
+        int r0, nr, c0, nc;
+        ray_rect(ang, U, cosa, r0, nr, c0, nc);
+        L.rows[lane] = r0;
+        L.cols[lane] = c0;
+        L.ncol[lane] = nc;
+        items = nr > 0 && nc > 0 ? nr * nc : 0;
+    }
+    const int incl = wave_incl_scan(items, lane);
+    L.pref[lane] = incl;
+    __syncthreads();
+    const int total = __shfl(incl, 63, 64);
+    for (int k0 = 0; k0 < total; k0 += 64) {
+        const int k = k0 + lane;
+        if (k >= total) continue;
+        int lo = 0, hi = n - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (L.pref[mid] > k) hi = mid;
+            else lo = mid + 1;
+        }
+        const int p = lo;
+        const int r = k - (p ? L.pref[p - 1] : 0);
+        const int nc = L.ncol[p];
+        int row = (int)(((float)r + 0.5f) * (1.0f / (float)nc));
+        if (row * nc > r) --row;
+        if ((row + 1) * nc <= r) ++row;
+        int col = L.cols[p] + (r - row * nc);
+        if (col >= ang.M2) col -= ang.M2;
+        const int l = (L.rows[p] + row) * ang.M2 + col;
+        const float4 d = ang.dir[l];
+        const float cosa = L.cone[3][p];
+        if (cosa > -1.5f && fmaf(d.x, L.cone[0][p], fmaf(d.y, L.cone[1][p], d.z * L.cone[2][p])) < cosa) continue;
+        const double *d64 = ang.dir64 + 3 * (size_t)l;
+        float cf[3];
+        const int sg = entry_cross(m, L, p, d, d64, xhv, xlv, cf, A.retests);
+        if (!sg) continue;
+        const float Sm = (cf[0] + cf[1]) + cf[2];
+        const float inv = __builtin_amdgcn_rcpf(Sm);
+        float rho = L.vol[p] * inv;
+        if (!(rho > 0.f) || !(rho < stop)) continue;
+        float P[3][3], Wv[3][3], w_in[3], ray[3] = {0.f, 0.f, 0.f};
+        int e[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            e[j] = L.id[j][p];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                P[j][c] = L.a[3 * j + c][p];
+                Wv[j][c] = L.w[3 * j + c][p];
+            }
+        }
+        const float lp = cf[1] * inv, lq = cf[2] * inv, lr = cf[0] * inv;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) w_in[c] = fmaf(lp, Wv[0][c], fmaf(lq, Wv[1][c], lr * Wv[2][c]));
+        int T = L.tet[p];
+        walk_ray<PREC, LISTED>(m, th, all_pairs, d, d64, xhv, xlv, L.list, nlist, stop, sg, T, e, P, Wv, cf, w_in, rho, ray,
+                               A);
+        if (PREC == 1) acc_add<1>(A, ray[0], ray[1], ray[2]);
+    }
+    __syncthreads();
+}
+
+template <int PREC, bool LISTED>
+__global__ void __launch_bounds__(64) k_rt_reenter(DevMesh m, Thresholds th, AngTab ang, BoundaryFaces bf, int all_pairs,
+                                                   float r_stop, double *__restrict__ rtv,
+                                                   unsigned long long *__restrict__ cnt, const int *__restrict__ node_list,
+                                                   const unsigned long long *__restrict__ node_count,
+                                                   const int *__restrict__ sel_list, const int *__restrict__ sel_n)
+{
+    __shared__ EntryLds L;
+    const int lane = threadIdx.x;
+    const int count = (int)*node_count;
+    const int ngrp = (bf.n + 63) / 64;
+    for (int nk = blockIdx.x; nk < count; nk += gridDim.x) {
+        const int self = node_list[m.n - 1 - nk];
+        float xhv[3], xlv[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            xhv[c] = m.xh[c * m.npad + self];
+            xlv[c] = m.xl[c * m.npad + self];
+        }
+        RtAcc A;
+        A.ax = A.ay = A.az = A.sx = A.sy = A.sz = A.cx = A.cy = A.cz = 0.f;
+        A.dx = A.dy = A.dz = 0.0;
+        A.pairs = A.hits = 0;
+        A.retests = 0;
+        int nlist = 0;
+        if constexpr (LISTED) {
+            nlist = sel_n[self];
+            for (int k = lane; k < nlist; k += 64) L.list[k] = sel_list[(size_t)self * kSelCap + k];
+            __syncthreads();
+            sort_list(L.list, nlist, lane);
+        }
+        int ncand = 0; // uniform
+        for (int g0 = 0; g0 < ngrp; g0 += 64) {
+            bool near = false;
+            if (g0 + lane < ngrp) {
+                const float4 sp = bf.sph[g0 + lane];
+                const float dx = sp.x - xhv[0], dy = sp.y - xhv[1], dz = sp.z - xhv[2];
+                const float rr = (sp.w + r_stop) * (1.f + 1e-5f);
+                near = all_pairs || (dx * dx + dy * dy) + dz * dz < rr * rr;
+            }
+            for (unsigned long long todo = __ballot(near); todo; todo &= todo - 1ull) {
+                const int k = 64 * (g0 + __builtin_ctzll(todo)) + lane;
+                bool take = false;
+                if (k < bf.n) {
+                    const int2 bk = bf.face[k];
+                    const int4 id4 = m.tid[bk.x];
+                    const int id[4] = {id4.x, id4.y, id4.z, id4.w};
+                    float a[3][3];
+                    int q = 0;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (j != (bk.y & 3)) {
+                            const float4 r0 = m.nrec[2 * id[j]], r1 = m.nrec[2 * id[j] + 1];
+                            a[q][0] = (r0.x - xhv[0]) + (r0.w - xlv[0]);
+                            a[q][1] = (r0.y - xhv[1]) + (r1.x - xlv[1]);
+                            a[q][2] = (r0.z - xhv[2]) + (r1.y - xlv[2]);
+                            ++q;
+                        }
+                    float N[3];
+                    cross_canon(a[1], a[2], N);
+                    const float vol = fmaf(a[0][0], N[0], fmaf(a[0][1], N[1], a[0][2] * N[2]));
+                    // the inner side of the face sees [a_p, a_q, a_r] positive
+                    // (bit 2 clear) or negative; a face with the node as a
+                    // vertex is crossed by none of its rays
+                    const bool mine = (id4.x == self) | (id4.y == self) | (id4.z == self) | (id4.w == self);
+                    take = !mine && ((bk.y & 4) ? vol > 0.f : vol < 0.f);
+                }
+                list_append(L.cand, ncand, take, k, lane);
+                __syncthreads();
+                if (ncand >= 64) {
+                    entry_batch<PREC, LISTED>(m, th, ang, bf, L, 64, nlist, all_pairs, r_stop, lane, xhv, xlv, A);
+                    list_shift(L.cand, ncand, 64, lane);
+                }
+            }
+        }
+        if (ncand > 0) entry_batch<PREC, LISTED>(m, th, ang, bf, L, ncand, nlist, all_pairs, r_stop, lane, xhv, xlv, A);
+
+        double vx, vy, vz;
+        if (PREC == 0) {
+            vx = A.ax;
+            vy = A.ay;
+            vz = A.az;
+        } else if (PREC == 1) {
+            vx = (double)A.sx + (double)A.cx;
+            vy = (double)A.sy + (double)A.cy;
+            vz = (double)A.sz + (double)A.cz;
+        } else {
+            vx = A.dx;
+            vy = A.dy;
+            vz = A.dz;
+        }
+        vx = wave_sum_f64(vx);
+        vy = wave_sum_f64(vy);
+        vz = wave_sum_f64(vz);
+        const unsigned long long hits = wave_sum_u64(A.hits);
+        const unsigned long long rts = wave_sum_u64((unsigned long long)A.retests);
+        if (lane == 0) {
+            rtv[self] += vx;
+            rtv[m.npad + self] += vy;
+            rtv[2 * m.npad + self] += vz;
+            if (cnt) {
+                unsigned long long *c = cnt_copy(cnt, self);
+                atomicAdd(&c[3], hits);
+                atomicAdd(&c[4], rts);
+            }
+        }
+        __syncthreads(); // the next node reuses the shared arrays
+    }
+}
+
 hipError_t launch_rt(const DevMesh &m, const Thresholds &th, const AngTab &ang, const LearnParams &lp,
                      int all_pairs, int precision, double *rtv, unsigned long long *cnt, const int *node_list,
                      const int *node_count, hipStream_t s)
@@ -2602,14 +2942,14 @@ hipError_t launch_select(const DevMesh &m, const Thresholds &th, const LearnPara
 }
 
 hipError_t launch_rt_walk(const DevMesh &m, const Thresholds &th, const AngTab &ang, int all_pairs, float r_stop,
-                          int exit_fb, int precision, double *rtv, unsigned long long *cnt, int *fallback,
-                          int *n_fallback, const int *sel_list, const int *sel_n, const float *sel_dmax,
+                          unsigned long long *n_reenter, int precision, double *rtv, unsigned long long *cnt,
+                          int *fallback, int *n_fallback, const int *sel_list, const int *sel_n, const float *sel_dmax,
                           const int *sel_cnt, hipStream_t s)
 {
     if (m.n == 0) return hipSuccess;
     const bool L = sel_n != nullptr;
 #define BS_RW(P, LL)                                                                                               \
-    hipLaunchKernelGGL((k_rt_walk<P, LL>), dim3(m.n), dim3(64), 0, s, m, th, ang, all_pairs, r_stop, exit_fb, rtv, \
+    hipLaunchKernelGGL((k_rt_walk<P, LL>), dim3(m.n), dim3(64), 0, s, m, th, ang, all_pairs, r_stop, n_reenter, rtv, \
                        cnt, fallback, n_fallback, sel_list, sel_n, sel_dmax, sel_cnt)
     if (precision == 0) {
         if (L) BS_RW(0, true); else BS_RW(0, false);
@@ -2619,6 +2959,28 @@ hipError_t launch_rt_walk(const DevMesh &m, const Thresholds &th, const AngTab &
         if (L) BS_RW(2, true); else BS_RW(2, false);
     }
 #undef BS_RW
+    return hipGetLastError();
+}
+
+hipError_t launch_rt_reenter(const DevMesh &m, const Thresholds &th, const AngTab &ang, const BoundaryFaces &bf,
+                             int all_pairs, float r_stop, int precision, double *rtv, unsigned long long *cnt,
+                             const int *list, const unsigned long long *count, const int *sel_list, const int *sel_n,
+                             hipStream_t s)
+{
+    if (m.n == 0) return hipSuccess;
+    const bool L = sel_n != nullptr;
+    const int grid = std::min(m.n, kRtListGrid);
+#define BS_RE(P, LL)                                                                                                \
+    hipLaunchKernelGGL((k_rt_reenter<P, LL>), dim3(grid), dim3(64), 0, s, m, th, ang, bf, all_pairs, r_stop, rtv, cnt, \
+                       list, count, sel_list, sel_n)
+    if (precision == 0) {
+        if (L) BS_RE(0, true); else BS_RE(0, false);
+    } else if (precision == 1) {
+        if (L) BS_RE(1, true); else BS_RE(1, false);
+    } else {
+        if (L) BS_RE(2, true); else BS_RE(2, false);
+    }
+#undef BS_RE
     return hipGetLastError();
 }
 

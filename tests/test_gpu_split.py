@@ -6,7 +6,7 @@ decades in one mesh, and an extent beyond the contraction's number range
 
 Tolerances as in the parity tests: relative L2 error 1e-6 over all nodes, and
 at every node 5e-6 of the larger of its own and the root-mean-square
-velocity."""
+velocity.  Also rays that leave the mesh and enter it again."""
 import numpy as np
 import pytest
 
@@ -74,3 +74,30 @@ def test_points_far_outside(far):
     v, _ = run(xyz, om, m.tets, cuts={})
     compare(v[:512], ref[:512], "mesh")
     compare(v[512:], ref[512:], "far points")
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+@pytest.mark.parametrize("kind", ["pure_rt", "fixed"])
+def test_rays_entering_the_mesh_again(kind, prec):
+    """A box with a slot cut out and a hole: rays leave the mesh and enter it
+    again, some twice, and the nodes inside the cut belong to no tet.
+    (Precision 0 sums in plain binary32: ten times the tolerance.)"""
+    m = W.make_config("C1", scale=(9, 8, 7))
+    c = m.xyz[m.tets].mean(axis=1)
+    cut = ((np.abs(c[:, 0]) < 0.35) & (c[:, 1] > -0.3)) | (np.linalg.norm(c - [0.6, 0.4, 0.1], axis=1) < 0.3)
+    tets = np.ascontiguousarray(m.tets[~cut])
+    h = bs.bs_mesh_upload(m.xyz, m.omega, tets)
+    k = bs.BS_POLICY_PURE_RT if kind == "pure_rt" else bs.BS_POLICY_FIXED
+    bs.bs_set_policy(h, kind=k, n_phi=8, n_theta=12, precision=prec)
+    v, st = bs.bs_eval_velocity(h, stats=True)
+    bs.bs_mesh_free(h)
+    ref, cnt = oracle.evaluate(m.xyz, m.omega, tets, oracle.make_policy(kind, n_phi=8, n_theta=12),
+                               return_counters=True)
+    assert st["pairs_by_rule"] == cnt["pairs_by_rule"]
+    e = float(np.linalg.norm(v - ref) / np.linalg.norm(ref))
+    scale = np.sqrt(np.mean(np.sum(ref * ref, axis=1)))
+    worst = float((np.linalg.norm(v - ref, axis=1) / np.maximum(np.linalg.norm(ref, axis=1), scale)).max())
+    print(f"  {kind} precision {prec}: {st['rt_walk_nodes']} walked, {st['rt_candidate_nodes']} with candidate rays, "
+          f"rel-L2 {e:.3e}, worst node {worst:.3e}", flush=True)
+    f = 1 if prec else 10
+    assert e <= 1e-6 * f and worst <= 5e-6 * f, (e, worst)
