@@ -36,9 +36,20 @@ namespace bsk {
 // exact velocity of one tet at the origin (vertices a[j] relative to x,
 // vorticity w[j]) by the signed-cone decomposition; tri: collapsed Gauss rule
 // on the reference triangle (u, v, weight), nq points.
-__device__ void cone_reference(const double (&a)[4][3], const double (&w)[4][3], const double *tri, int nq,
-                               double *out)
+// (four neighbouring lanes per pair, lane f of them on face f; all get out)
+__device__ __forceinline__ void cone_reference(const double (&a0)[4][3], const double (&w0)[4][3], const double *tri,
+                                               int nq, int f, double *out)
 {
+    // (local copies stay in registers; selects between elements of an argument
+    // array become indexed scratch loads)
+    double a[4][3], w[4][3];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            a[j][k] = a0[j][k];
+            w[j][k] = w0[j][k];
+        }
     // vorticity extended to x: barycentric weights of the origin
     double vol[4];
 #pragma unroll
@@ -54,24 +65,32 @@ __device__ void cone_reference(const double (&a)[4][3], const double (&w)[4][3],
     double wx[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) wx[k] = lam[0] * w[0][k] + lam[1] * w[1][k] + lam[2] * w[2][k] + lam[3] * w[3][k];
-    double acc[3] = {0.0, 0.0, 0.0};
-    for (int f = 0; f < 4; ++f) {
-        const int p = f == 0 ? 1 : 0, q = f <= 1 ? 2 : 1, r = f <= 2 ? 3 : 2;
-        double e1[3], e2[3], n[3];
+    // this lane's face f: vertices p < q < r, opposite vertex o
+    double ap[3], aq[3], ar[3], ao[3], wp[3], wq[3], wr[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            e1[k] = a[q][k] - a[p][k];
-            e2[k] = a[r][k] - a[p][k];
-        }
-        n[0] = e1[1] * e2[2] - e1[2] * e2[1];
-        n[1] = e1[2] * e2[0] - e1[0] * e2[2];
-        n[2] = e1[0] * e2[1] - e1[1] * e2[0];
-        const double area2 = sqrt(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
-        // signed distance of x (origin) from the plane, and of the opposite vertex
-        const double dx = -(n[0] * a[p][0] + n[1] * a[p][1] + n[2] * a[p][2]) / area2;
-        const double dv = (n[0] * (a[f][0] - a[p][0]) + n[1] * (a[f][1] - a[p][1]) + n[2] * (a[f][2] - a[p][2])) /
-                          area2;
-        if (dx == 0.0) continue;
+    for (int k = 0; k < 3; ++k) {
+        ap[k] = f == 0 ? a[1][k] : a[0][k];
+        aq[k] = f <= 1 ? a[2][k] : a[1][k];
+        ar[k] = f <= 2 ? a[3][k] : a[2][k];
+        ao[k] = f == 0 ? a[0][k] : f == 1 ? a[1][k] : f == 2 ? a[2][k] : a[3][k];
+        wp[k] = f == 0 ? w[1][k] : w[0][k];
+        wq[k] = f <= 1 ? w[2][k] : w[1][k];
+        wr[k] = f <= 2 ? w[3][k] : w[2][k];
+    }
+    double e1[3], e2[3], n[3], part[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        e1[k] = aq[k] - ap[k];
+        e2[k] = ar[k] - ap[k];
+    }
+    n[0] = e1[1] * e2[2] - e1[2] * e2[1];
+    n[1] = e1[2] * e2[0] - e1[0] * e2[2];
+    n[2] = e1[0] * e2[1] - e1[1] * e2[0];
+    const double area2 = sqrt(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
+    // signed distance of x (origin) from the plane, and of the opposite vertex
+    const double dx = -(n[0] * ap[0] + n[1] * ap[1] + n[2] * ap[2]) / area2;
+    const double dv = (n[0] * (ao[0] - ap[0]) + n[1] * (ao[1] - ap[1]) + n[2] * (ao[2] - ap[2])) / area2;
+    if (dx != 0.0) {
         const double sg = ((dx > 0) == (dv > 0)) ? 1.0 : -1.0;
         const double hF = fabs(dx);
         double fa[3] = {0.0, 0.0, 0.0};
@@ -81,8 +100,8 @@ __device__ void cone_reference(const double (&a)[4][3], const double (&w)[4][3],
             double P[3], W[3];
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                P[k] = a[p][k] + u * e1[k] + v * e2[k];
-                W[k] = 0.5 * (wx[k] + (l0 * w[p][k] + u * w[q][k] + v * w[r][k]));
+                P[k] = ap[k] + u * e1[k] + v * e2[k];
+                W[k] = 0.5 * (wx[k] + (l0 * wp[k] + u * wq[k] + v * wr[k]));
             }
             const double R2 = P[0] * P[0] + P[1] * P[1] + P[2] * P[2];
             const double s = wt * hF / (R2 * sqrt(R2));
@@ -91,8 +110,13 @@ __device__ void cone_reference(const double (&a)[4][3], const double (&w)[4][3],
             fa[2] += s * (P[0] * W[1] - P[1] * W[0]);
         }
 #pragma unroll
-        for (int k = 0; k < 3; ++k) acc[k] += sg * area2 * fa[k];
+        for (int k = 0; k < 3; ++k) part[k] = sg * area2 * fa[k];
     }
+    // the faces in order
+    double acc[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        acc[k] = (((0.0 + __shfl(part[k], 0, 4)) + __shfl(part[k], 1, 4)) + __shfl(part[k], 2, 4)) + __shfl(part[k], 3, 4);
     const double c = 1.0 / (4.0 * M_PI);
 #pragma unroll
     for (int k = 0; k < 3; ++k) out[k] = acc[k] * c;
@@ -121,13 +145,18 @@ __device__ void gauss_value(const double (&a)[4][3], const double (&w)[4][3], co
     }
 }
 
-__global__ void __launch_bounds__(64) k_label(DevMesh m, const int2 *__restrict__ pairs, int n, float hbar,
+// Four lanes per pair: lane f integrates face f of the reference and, f < 3,
+// evaluates rule f.  (One lane per pair left one wave on every SIMD for 65,536
+// pairs, the latency of each point's square root and division exposed: 741 us
+// against 470.)  Bound by the FP64 square roots and divisions.
+__global__ void __launch_bounds__(256) k_label(DevMesh m, const int2 *__restrict__ pairs, int n, float hbar,
                                               const double *__restrict__ tri, int nq, const float *__restrict__ rules,
                                               double tau, float *__restrict__ feats, int8_t *__restrict__ labels,
                                               float *__restrict__ errs)
 {
-    const int k = blockIdx.x * 64 + threadIdx.x;
-    if (k >= n) return;
+    const int f4 = threadIdx.x & 3;
+    const int k = blockIdx.x * 64 + (threadIdx.x >> 2);
+    if (k >= n) return; // (all four lanes)
     const int2 pr = pairs[k];
     const int self = pr.x, t = pr.y;
     const int4 id4 = m.tid[t];
@@ -147,12 +176,14 @@ __global__ void __launch_bounds__(64) k_label(DevMesh m, const int2 *__restrict_
             wd[j][c] = (double)m.om[c * m.npad + id[j]];
         }
     }
-    float f[16];
-    pair_features(af, hbar, inc, f);
+    if (f4 == 3) {
+        float f[16];
+        pair_features(af, hbar, inc, f);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) feats[(size_t)k * 16 + q] = f[q];
+        for (int q = 0; q < 16; ++q) feats[(size_t)k * 16 + q] = f[q];
+    }
     double ref[3];
-    cone_reference(ad, wd, tri, nq, ref);
+    cone_reference(ad, wd, tri, nq, f4, ref);
     // |T| from the relative positions
     double e[3][3];
 #pragma unroll
@@ -165,25 +196,26 @@ __global__ void __launch_bounds__(64) k_label(DevMesh m, const int2 *__restrict_
     const double rn = sqrt(ref[0] * ref[0] + ref[1] * ref[1] + ref[2] * ref[2]);
     // rule table: barycentric points of the 1-, 4- and 11-point rules (16 x 4),
     // then their 16 weights
-    const int npts[3] = {1, 4, 11};
-    const int off[3] = {0, 1, 5};
-    int label = 3; // ray tracing unless a Gauss rule meets the budget
-    for (int r = 2; r >= 0; --r) {
+    double er = 0.0;
+    if (f4 < 3) {
+        const int off = f4 == 0 ? 0 : f4 == 1 ? 1 : 5, npts = f4 == 0 ? 1 : f4 == 1 ? 4 : 11;
         double g[3];
-        gauss_value(ad, wd, rules + 4 * off[r], rules + 64 + off[r], npts[r], vol, g);
+        gauss_value(ad, wd, rules + 4 * off, rules + 64 + off, npts, vol, g);
         const double dx = g[0] - ref[0], dy = g[1] - ref[1], dz = g[2] - ref[2];
-        const double er = sqrt(dx * dx + dy * dy + dz * dz) / fmax(rn, 1e-300);
-        errs[(size_t)k * 3 + r] = (float)er;
-        if (er <= tau) label = r; // scanning down: the cheapest qualifying rule wins
+        er = sqrt(dx * dx + dy * dy + dz * dz) / fmax(rn, 1e-300);
+        errs[(size_t)k * 3 + f4] = (float)er;
     }
-    labels[k] = (int8_t)label;
+    int label = 3; // ray tracing unless a Gauss rule meets the budget
+    for (int r = 2; r >= 0; --r)
+        if (__shfl(er, r, 4) <= tau) label = r; // scanning down: the cheapest qualifying rule wins
+    if (f4 == 0) labels[k] = (int8_t)label;
 }
 
 hipError_t launch_label(const DevMesh &m, const int2 *pairs, int n, float hbar, const double *tri, int nq,
                         const float *rules, double tau, float *feats, int8_t *labels, float *errs, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_label, dim3((n + 63) / 64), dim3(64), 0, s, m, pairs, n, hbar, tri, nq, rules, tau, feats,
+    hipLaunchKernelGGL(k_label, dim3((n + 63) / 64), dim3(256), 0, s, m, pairs, n, hbar, tri, nq, rules, tau, feats,
                        labels, errs);
     return hipGetLastError();
 }
@@ -366,12 +398,26 @@ __global__ void __launch_bounds__(256) k_mlp_adam(const float *__restrict__ gpar
                                                   float beta1, float beta2, float eps, float bc1, float bc2,
                                                   float *__restrict__ grad_out)
 {
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= kMlpGradLen) return;
+    // 32 parameters per workgroup; eight row groups take every eighth block's
+    // partials, their sums added in order (one thread per parameter over 1,024
+    // blocks took 249 us, this 14)
+    __shared__ double sg[8][32], sw[8][32];
+    const int c = threadIdx.x & 31, rg = threadIdx.x >> 5;
+    const int j = blockIdx.x * 32 + c;
+    const int jc = min(j, kMlpGradLen - 1);
     double W = 0.0, g = 0.0;
-    for (int b = 0; b < nblocks; ++b) {
+#pragma unroll 4
+    for (int b = rg; b < nblocks; b += 8) {
         W += (double)wpart[b];
-        g += (double)gpart[(size_t)b * kMlpGradLen + j];
+        g += (double)gpart[(size_t)b * kMlpGradLen + jc];
+    }
+    sg[rg][c] = g;
+    sw[rg][c] = W;
+    __syncthreads();
+    if (rg != 0 || j >= kMlpGradLen) return;
+    for (int r = 1; r < 8; ++r) {
+        g += sg[r][c];
+        W += sw[r][c];
     }
     const float gr = W > 0.0 ? (float)(g / W) : 0.f;
     if (grad_out) grad_out[j] = gr;
@@ -385,13 +431,12 @@ __global__ void __launch_bounds__(256) k_mlp_adam(const float *__restrict__ gpar
     wb[32 + j] = (__bf16)w;
 }
 
-__global__ void k_sum_f(const float *__restrict__ a, int n, double *__restrict__ out)
+__global__ void __launch_bounds__(64) k_sum_f(const float *__restrict__ a, int n, double *__restrict__ out)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double s = 0.0;
-        for (int i = 0; i < n; ++i) s += a[i];
-        out[0] = s;
-    }
+    double s = 0.0;
+    for (int i = threadIdx.x; i < n; i += 64) s += a[i];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (threadIdx.x == 0) out[0] = s;
 }
 
 hipError_t launch_mlp_grad_step(const float *feats, const int8_t *labels, const int *index, int n, __bf16 *wb,
@@ -405,7 +450,7 @@ hipError_t launch_mlp_grad_step(const float *feats, const int8_t *labels, const 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const float bc1 = 1.f - powf(beta1, (float)step), bc2 = 1.f - powf(beta2, (float)step);
-    hipLaunchKernelGGL(k_mlp_adam, dim3((kMlpGradLen + 255) / 256), dim3(256), 0, s, gpart, wpart, nb, master, mom1,
+    hipLaunchKernelGGL(k_mlp_adam, dim3((kMlpGradLen + 31) / 32), dim3(256), 0, s, gpart, wpart, nb, master, mom1,
                        mom2, wb, lr, beta1, beta2, eps, bc1 > 0.f ? bc1 : 1.f, bc2 > 0.f ? bc2 : 1.f, grad_out);
     return hipGetLastError();
 }
