@@ -2149,32 +2149,26 @@ int read_stats(bs_mesh *m, bs_stats *st)
     return BS_OK;
 }
 
-// Nodal velocity gradient into m->ngrad ([n][3][3] FP64, input order) from
-// device velocities vel ([n][3], input order).
-int velocity_gradient_device(bs_mesh *m, const double *vel, hipStream_t s)
+// Nodal velocity gradient into grad ([n][3][3] FP64, input order; device) or,
+// with rate, the stretching rate G omega of every node into rate ([n][3]) from
+// device velocities vel ([n][3], input order) and the mesh's current
+// vorticity.  (The outputs may share vel's memory: it is read before they are
+// written.)
+int velocity_gradient_device(bs_mesh *m, const double *vel, double *grad, double *rate, hipStream_t s)
 {
     int rc;
-    if ((rc = dalloc(m->tgrad, 8 * 10 * (size_t)std::max<int64_t>(m->T, 1))) ||
-        (rc = dalloc(m->ngrad, 8 * 9 * (size_t)std::max<int64_t>(m->n, 1))))
-        return rc;
-    const bsk::DevMesh dm = dev_view(m);
-    hipError_t e = bsk::launch_velocity_gradient(dm, (const int *)m->node_orig.p, vel, (double *)m->tgrad.p,
-                                                 (double *)m->ngrad.p, s);
+    if ((rc = dalloc(m->tgrad, 8 * 10 * (size_t)std::max<int64_t>(m->T, 1)))) return rc;
+    const hipError_t e = bsk::launch_velocity_gradient(dev_view(m), (const int *)m->node_orig.p, vel,
+                                                       (double *)m->tgrad.p, grad, (const double *)m->om64.p, rate, s);
     if (e != hipSuccess) return hip_fail(e, "velocity gradient kernels");
     return BS_OK;
 }
 
-// Stretching rate G omega of every node into m->srate ([n][3] FP64, input
-// order) from device velocities vel ([n][3], input order) and the mesh's
-// current vorticity.
+// Stretching rate into m->srate.
 int stretching_device(bs_mesh *m, const double *vel, hipStream_t s)
 {
-    int rc = velocity_gradient_device(m, vel, s);
-    if (rc || (rc = dalloc(m->srate, 8 * 3 * (size_t)std::max<int64_t>(m->n, 1)))) return rc;
-    const hipError_t e = bsk::launch_stretching((int)m->n, (const double *)m->ngrad.p, (const double *)m->om64.p,
-                                                (double *)m->srate.p, s);
-    if (e != hipSuccess) return hip_fail(e, "stretching kernel");
-    return BS_OK;
+    const int rc = dalloc(m->srate, 8 * 3 * (size_t)std::max<int64_t>(m->n, 1));
+    return rc ? rc : velocity_gradient_device(m, vel, nullptr, (double *)m->srate.p, s);
 }
 
 } // namespace
@@ -2207,10 +2201,11 @@ int bs_velocity_gradient(bs_mesh *m, const double *vel, double *grad, uint32_t f
         }
     }
     if (m->n == 0) return BS_OK;
-    int rc = velocity_gradient_device(m, dvel, s);
-    if (rc) return rc;
-    if ((e = hipMemcpyAsync(grad, m->ngrad.p, 8 * 9 * (size_t)m->n,
-                            (flags & BS_PTR_DEVICE) ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s)) ||
+    const bool dev = flags & BS_PTR_DEVICE;
+    int rc;
+    if (!dev && (rc = dalloc(m->ngrad, 8 * 9 * (size_t)m->n))) return rc;
+    if ((rc = velocity_gradient_device(m, dvel, dev ? grad : (double *)m->ngrad.p, nullptr, s))) return rc;
+    if ((!dev && (e = hipMemcpyAsync(grad, m->ngrad.p, 8 * 9 * (size_t)m->n, hipMemcpyDeviceToHost, s))) ||
         (e = hipStreamSynchronize(s)))
         return hip_fail(e, "velocity gradient");
     return BS_OK;
@@ -2242,10 +2237,10 @@ int bs_stretching_rate(bs_mesh *m, const double *vel, double *rate, uint32_t fla
         }
     }
     if (m->n == 0) return BS_OK;
-    int rc = stretching_device(m, dvel, s);
+    const bool dev = flags & BS_PTR_DEVICE;
+    const int rc = dev ? velocity_gradient_device(m, dvel, nullptr, rate, s) : stretching_device(m, dvel, s);
     if (rc) return rc;
-    if ((e = hipMemcpyAsync(rate, m->srate.p, 8 * n3,
-                            (flags & BS_PTR_DEVICE) ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s)) ||
+    if ((!dev && (e = hipMemcpyAsync(rate, m->srate.p, 8 * n3, hipMemcpyDeviceToHost, s))) ||
         (e = hipStreamSynchronize(s)))
         return hip_fail(e, "stretching rate");
     return BS_OK;

@@ -159,11 +159,10 @@ hipError_t launch_rt_reenter(const DevMesh &m, const Thresholds &th, const AngTa
                              hipStream_t s);
 // Nodal velocity gradient (grad[input node][3][3], FP64) of the linear
 // interpolant of vel ([input node][3]) on each tet, volume-weighted over the
-// node's tets; tg: scratch of 10 doubles per tet.
+// node's tets; with rate, the vortex stretching rate rate[i] = G om[i] (input
+// order, FP64) instead.  tg: scratch of 10 doubles per tet.
 hipError_t launch_velocity_gradient(const DevMesh &m, const int *node_orig, const double *vel, double *tg,
-                                    double *grad, hipStream_t s);
-// Vortex stretching rate rate[i] = grad[i] om[i] (input order, FP64).
-hipError_t launch_stretching(int n, const double *grad, const double *om, double *rate, hipStream_t s);
+                                    double *grad, const double *om, double *rate, hipStream_t s);
 hipError_t launch_combine(const DevMesh &m, const int *node_orig, const double *part, int splits,
                           const double *band, int nsplit, const double *rtv, double *vel, int *nonfinite,
                           hipStream_t s);
