@@ -315,9 +315,10 @@ struct bs_mesh {
     // device buffers
     DBuf tsph; // bounding spheres of 16-tet tiles
     DBuf xh, xl, om, nrec, blk, node_orig, g1, g4, g11, tid, cell_start, nbr, inc_start, inc_list, bface, bsph;
+    bool inc_walkable = false;       // every node has 1 .. kIncCap incident tets (the walk leaves none to k_rt)
     int nbface = 0;                  // boundary faces in bface (0 where the boundary is convex)
     std::vector<int64_t> bface_in;   // 4 * tet + face of every boundary face, input numbering
-    DBuf part, band, rtv, vel, cnt, nonfinite, fallback;
+    DBuf part, band, rtv, vel, cnt, fallback;
     // evaluation points (bs_eval_points): FP64 copy, count, first node index
     // and first block in the node arrays, their order and output
     std::vector<double> tgt;
@@ -1325,6 +1326,11 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
         const int32_t i = orig[(size_t)r];
         inc_start[(size_t)r + 1] = inc_start[(size_t)r] + (m->inc_in_start[(size_t)i + 1] - m->inc_in_start[(size_t)i]);
     }
+    m->inc_walkable = true;
+    for (int64_t r = 0; r < n; ++r) {
+        const int32_t ninc = inc_start[(size_t)r + 1] - inc_start[(size_t)r];
+        if (ninc < 1 || ninc > bsk::kIncCap) m->inc_walkable = false;
+    }
     parallel_for(n, [&](int64_t a, int64_t b) {
         for (int64_t r = a; r < b; ++r) {
             const int32_t i = orig[(size_t)r], c0 = m->inc_in_start[(size_t)i], c1 = m->inc_in_start[(size_t)i + 1];
@@ -1386,8 +1392,8 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
         (rc = dalloc(m->torig, 4 * torig.size())) || (rc = dalloc(m->tlist, 4 * tlist.size())) ||
         (rc = dalloc(m->tvel, 8 * 3 * (size_t)tn)) || (rc = dalloc(m->tid, sizeof(int4) * (size_t)T)) ||
         (rc = dalloc(m->cell_start, 4 * cell_start.size())) ||
-        (rc = dalloc(m->rtv, 8 * 3 * (size_t)npad)) || (rc = dalloc(m->vel, 8 * 3 * (size_t)n)) ||
-        (rc = dalloc(m->cnt, 8 * bsk::kCntWords)) || (rc = dalloc(m->nonfinite, 4)) ||
+        (rc = dalloc(m->vel, 8 * 3 * (size_t)n)) ||
+        (rc = dalloc(m->cnt, 8 * bsk::kCntWords)) ||
         (rc = dalloc(m->nbr, sizeof(int4) * (size_t)T)) ||
         (rc = dalloc(m->tsph, sizeof(float4) * tsph.size())) || (rc = dalloc(m->inc_start, 4 * inc_start.size())) ||
         (rc = dalloc(m->bface, sizeof(int2) * std::max<size_t>(bface.size(), 1))) ||
@@ -1747,7 +1753,7 @@ void bs_mesh_free(bs_mesh *m)
     if (!m) return;
     DBuf *bufs[] = {&m->xh, &m->xl, &m->om, &m->nrec, &m->tsph, &m->blk, &m->node_orig, &m->g1, &m->g4, &m->g11, &m->tid,
                     &m->nbr, &m->inc_start, &m->inc_list, &m->fallback,
-                    &m->cell_start, &m->bface, &m->bsph, &m->part, &m->band, &m->rtv, &m->vel, &m->cnt, &m->nonfinite, &m->dir,
+                    &m->cell_start, &m->bface, &m->bsph, &m->part, &m->band, &m->rtv, &m->vel, &m->cnt, &m->dir,
                     &m->dir64, &m->cphi, &m->dia, &m->mlp, &m->sel, &m->torig, &m->tlist, &m->tvel,
                     &m->gvel, &m->tgrad, &m->ngrad, &m->om64, &m->srate,
                     &m->tree.nrange, &m->tree.child, &m->tree.leaves, &m->tree.c64, &m->tree.crec,
@@ -1846,6 +1852,15 @@ int band_splits(const bs_mesh *m, int64_t nblk)
     return (int)std::min<int64_t>(32, std::max<int64_t>(4, 12 * 1792 / nblk));
 }
 
+// Workgroups (waves) per node of the ray-tracing walk: the chip holds 4,096 of
+// them (four per SIMD), so a mesh of fewer nodes gives each node's blocks of
+// rays to up to four (1,331 nodes: 184 us with one, 111 with four).
+int walk_waves(const bs_mesh *m)
+{
+    if (!m->manifold || !m->convex || m->n <= 0) return 1;
+    return (int)std::min<int64_t>(4, std::max<int64_t>(1, 8192 / m->n));
+}
+
 // Device buffers of one evaluation that the caller provides instead of the
 // mesh (the no-allocation entry point): partial sums, counters, the walk's
 // fallback list and the learned policy's lists, and the output.
@@ -1853,7 +1868,7 @@ struct EvalBufs {
     int nsplit; // of the band kernel
     double *part, *band, *rtv, *vel;
     unsigned long long *cnt;
-    int *nonfinite, *fallback, *sel;
+    int *fallback, *sel;
 };
 
 // Scales of the split contraction (bs_split_dev.h) for pairs no closer than
@@ -1885,7 +1900,7 @@ void split_scales(const bs_mesh *m, double cut, double eps, bsk::Thresholds &th)
 // of the nodes; their velocities go to m->tvel.  With given buffers (nodes
 // only) nothing is allocated: the buffers come from `given`, counters are
 // cleared by a kernel, every kernel runs on s and no event is recorded.
-int eval_device(bs_mesh *m, hipStream_t s, bool targets, const EvalBufs *given = nullptr)
+int eval_device(bs_mesh *m, hipStream_t s, bool targets, double *out2 = nullptr, const EvalBufs *given = nullptr)
 {
     int rc;
     if (given) {
@@ -1914,9 +1929,11 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, const EvalBufs *given =
     if (!given && fixed_like && (rc = dalloc(m->band, 8 * 3 * (size_t)m->npad * nsplit))) return rc;
     double *b_part = given ? given->part : (double *)m->part.p;
     double *b_band = given ? given->band : (double *)m->band.p;
-    double *b_rtv = given ? given->rtv : (double *)m->rtv.p;
     unsigned long long *cnt = given ? given->cnt : (unsigned long long *)m->cnt.p;
-    int *b_nonfinite = given ? given->nonfinite : (int *)m->nonfinite.p;
+    int *b_nonfinite = (int *)(cnt + 10);
+    const int nwave = targets ? 1 : walk_waves(m);
+    if (!given && (rc = dalloc(m->rtv, 8 * 3 * (size_t)m->npad * nwave))) return rc;
+    double *b_rtv = given ? given->rtv : (double *)m->rtv.p;
     bsk::Thresholds th{};
     const double hb = m->hbar;
     const double c_rt = P.near_cut * hb, c_11 = P.d_g11 * hb, c_4 = P.d_g4 * hb;
@@ -1953,13 +1970,8 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, const EvalBufs *given =
     ang.M2 = 2 * P.n_theta;
 
     hipError_t e;
-    if (given) {
-        if ((e = bsk::launch_fill_zero(cnt, 2 * bsk::kCntWords, s)) ||
-            (e = bsk::launch_fill_zero(b_nonfinite, 1, s)))
-            return hip_fail(e, "clear counters");
-    } else if ((e = hipMemsetAsync(cnt, 0, 8 * bsk::kCntWords, s)) || (e = hipMemsetAsync(b_nonfinite, 0, 4, s))) {
+    if ((e = given ? bsk::launch_fill_zero(cnt, 2 * bsk::kCntWords, s) : hipMemsetAsync(cnt, 0, 8 * bsk::kCntWords, s)))
         return hip_fail(e, "clear counters");
-    }
     const double *part = nullptr, *band = nullptr, *rtv = nullptr;
     const bool one_stream = m->serial || given;
     auto record = [&](int k, hipStream_t st) {
@@ -2025,9 +2037,9 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, const EvalBufs *given =
         // the boundary faces through which it can enter again
         if (m->manifold && m->rt_mode == 0 && !targets) {
             m->last_rt = 2;
-            if (!given && (rc = dalloc(m->fallback, 4 * ((size_t)m->n + 1)))) return rc;
+            if (!given && (rc = dalloc(m->fallback, 4 * (size_t)m->n))) return rc;
             int *fb = given ? given->fallback : (int *)m->fallback.p;
-            int *nfb = fb + m->n;
+            int *nfb = (int *)(cnt + 9);
             const float r_stop = all ? 3.0e38f : (float)((std::max(c_rt, m->max_vc) + m->max_vc) * (1.0 + 1e-4) + 1e-6);
             int *sel_list = nullptr, *sel_n = nullptr, *sel_cnt = nullptr;
             float *sel_dmax = nullptr;
@@ -2039,12 +2051,12 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, const EvalBufs *given =
                 sel_dmax = (float *)(sel_n + nn);
                 sel_cnt = (int *)(sel_dmax + nn);
             }
-            if ((e = given ? bsk::launch_fill_zero(nfb, 1, sr) : hipMemsetAsync(nfb, 0, 4, sr)) ||
-                (lp.net && (e = bsk::launch_select(dm, th, lp, P.precision, b_rtv, sel_list, sel_n, sel_dmax,
+            if ((lp.net && (e = bsk::launch_select(dm, th, lp, P.precision, b_rtv, sel_list, sel_n, sel_dmax,
                                                    sel_cnt, sr))) ||
-                (e = bsk::launch_rt_walk(dm, th, ang, all, r_stop, m->convex ? nullptr : cnt + 8, P.precision, b_rtv, cnt,
-                                         fb, nfb, sel_list, sel_n, sel_dmax, sel_cnt, sr)) ||
-                (e = bsk::launch_rt(dm, th, ang, lp, all, P.precision, b_rtv, cnt, fb, nfb, sr)) ||
+                (e = bsk::launch_rt_walk(dm, th, ang, all, r_stop, m->convex ? nullptr : cnt + 8, nwave, P.precision, b_rtv,
+                                         cnt, fb, nfb, sel_list, sel_n, sel_dmax, sel_cnt, sr)) ||
+                ((lp.net || !m->inc_walkable) &&
+                 (e = bsk::launch_rt(dm, th, ang, lp, all, P.precision, b_rtv, cnt, fb, nfb, sr))) ||
                 (!m->convex && (e = bsk::launch_rt_reenter(dm, th, ang,
                                                            {(const int2 *)m->bface.p, (const float4 *)m->bsph.p, m->nbface},
                                                            all, r_stop, P.precision, b_rtv, cnt, fb, cnt + 8, sel_list,
@@ -2057,15 +2069,15 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, const EvalBufs *given =
         }
         rtv = b_rtv;
     }
-    if (given) m->last_rt = 0; // (no statistics are read after a call that allocates nothing)
     record(5, sr);
     if (!one_stream && ((e = hipStreamWaitEvent(s, m->ev[3], 0)) || (e = hipStreamWaitEvent(s, m->ev[5], 0))))
         return hip_fail(e, "join streams");
     record(6, s);
     double *out = given ? given->vel : (double *)(targets ? m->tvel.p : m->vel.p);
     if ((e = bsk::launch_combine(dm, (const int *)(targets ? m->torig.p : m->node_orig.p), part, part ? splits : 0,
-                                 band, nsplit, rtv, out, b_nonfinite, s)))
+                                 band, nsplit, rtv, m->last_rt == 2 ? nwave : 1, out, out2, b_nonfinite, s)))
         return hip_fail(e, "combine kernel");
+    if (given) m->last_rt = 0; // (no statistics are read after a call that allocates nothing)
     record(7, s);
     if (!targets) m->vel_valid = !given;
     return BS_OK;
@@ -2079,8 +2091,8 @@ size_t eval_scratch_layout(const bs_mesh *m, int nsplit, size_t off[7])
 {
     auto al = [](size_t v) { return (v + 255) / 256 * 256; };
     const size_t np = (size_t)m->npad, nn = (size_t)m->n;
-    const size_t sz[7] = {8 * 3 * np * (size_t)far_splits(m), 8 * 3 * np * (size_t)nsplit, 8 * 3 * np, 8 * (size_t)bsk::kCntWords, 4,
-                          4 * (nn + 1),
+    const size_t sz[7] = {8 * 3 * np * (size_t)far_splits(m), 8 * 3 * np * (size_t)nsplit, 8 * 3 * np * (size_t)walk_waves(m),
+                          8 * (size_t)bsk::kCntWords, 4, 4 * (nn + 1),
                           m->pol.kind == BS_POLICY_LEARNED ? 4 * (nn * bsk::kSelListCap + 5 * nn) : 0};
     size_t o = 0;
     for (int k = 0; k < 7; ++k) {
@@ -2095,9 +2107,9 @@ int read_stats(bs_mesh *m, bs_stats *st)
     std::vector<unsigned long long> cc((size_t)bsk::kCntWords);
     int nf = 0;
     hipError_t e;
-    if ((e = hipMemcpy(cc.data(), m->cnt.p, 8 * cc.size(), hipMemcpyDeviceToHost)) ||
-        (e = hipMemcpy(&nf, m->nonfinite.p, 4, hipMemcpyDeviceToHost)))
+    if ((e = hipMemcpy(cc.data(), m->cnt.p, 8 * cc.size(), hipMemcpyDeviceToHost)))
         return hip_fail(e, "read counters");
+    nf = (int)cc[10];
     unsigned long long c[bsk::kNumCounters] = {};
     for (int k = 0; k < bsk::kCntStripes; ++k)
         for (int j = 0; j < bsk::kNumCounters; ++j) c[j] += cc[(size_t)(k * bsk::kCntStride + j)];
@@ -2132,10 +2144,8 @@ int read_stats(bs_mesh *m, bs_stats *st)
     st->hbar = m->hbar;
     const int64_t nt = m->last_targets ? m->tn : m->n;
     if (m->last_rt == 2) {
-        int nfb = 0;
-        if ((e = hipMemcpy(&nfb, (const int *)m->fallback.p + m->n, 4, hipMemcpyDeviceToHost)))
-            return hip_fail(e, "read counters");
-        nfb += (int)cc[8]; // nodes with rays that leave the mesh early
+        // nodes left to k_rt, and with rays that leave the mesh early
+        const int nfb = (int)cc[9] + (int)cc[8];
         st->rt_candidate_nodes = nfb;
         st->rt_walk_nodes = nt - nfb;
     } else if (m->last_rt == 1) {
@@ -2277,14 +2287,13 @@ int bs_eval_velocity(bs_mesh *m, double *vel, uint32_t vel_flags, void *stream, 
     hipStream_t s = (hipStream_t)stream;
     m->far_mode = (vel_flags & BS_EVAL_VALU_FAR) ? 1 : 0;
     m->serial = (vel_flags & BS_EVAL_SERIAL) ? 1 : 0;
-    int rc = eval_device(m, s, false);
+    const bool dev = vel_flags & BS_PTR_DEVICE;
+    int rc = eval_device(m, s, false, dev ? vel : nullptr);
     m->far_mode = 0;
     m->serial = 0;
     if (rc) return rc;
-    hipError_t e;
-    const size_t vbytes = 8 * 3 * (size_t)m->n;
-    e = hipMemcpyAsync(vel, m->vel.p, vbytes, (vel_flags & BS_PTR_DEVICE) ? hipMemcpyDeviceToDevice
-                                                                          : hipMemcpyDeviceToHost, s);
+    hipError_t e = hipSuccess;
+    if (!dev) e = hipMemcpyAsync(vel, m->vel.p, 8 * 3 * (size_t)m->n, hipMemcpyDeviceToHost, s);
     if (e != hipSuccess) return hip_fail(e, "copy velocity");
     if (!(vel_flags & BS_PTR_DEVICE) || st) {
         if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "evaluation");
@@ -2319,11 +2328,10 @@ int bs_eval_velocity_noalloc(bs_mesh *m, double *vel, uint32_t flags, void *stre
     g.band = (double *)(base + off[1]);
     g.rtv = (double *)(base + off[2]);
     g.cnt = (unsigned long long *)(base + off[3]);
-    g.nonfinite = (int *)(base + off[4]);
     g.fallback = (int *)(base + off[5]);
     g.sel = m->pol.kind == BS_POLICY_LEARNED ? (int *)(base + off[6]) : nullptr;
     g.vel = vel;
-    const int rc = eval_device(m, (hipStream_t)stream, false, &g);
+    const int rc = eval_device(m, (hipStream_t)stream, false, nullptr, &g);
     m->far_mode = 0;
     return rc;
 }

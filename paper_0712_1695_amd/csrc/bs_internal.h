@@ -100,7 +100,8 @@ struct DevMesh {
 // Counters accumulated by the kernels (device, 64-bit):
 // [0] G4 pairs, [1] G11 pairs, [2] RT pairs, [3] RT hit lines, [4] FP64 retests,
 // [5..7] pairs the learned selector moved from RT to G1 / G4 / G11.
-// [8] of the first copy: nodes listed for launch_rt_reenter.
+// In the first copy also [8] nodes listed for launch_rt_reenter, [9] nodes the
+// walk leaves to launch_rt, [10] non-finite output flag (32-bit).
 // Kept in kCntStripes copies, one 128-byte cache line each, a node or block
 // adding to copy (its index mod kCntStripes): atomics of every node on one
 // line serialise in the L2 and bound the per-node kernels.  The host sums
@@ -128,6 +129,7 @@ hipError_t launch_rt(const DevMesh &m, const Thresholds &th, const AngTab &ang, 
 // the selector moves (written to rtv) and the pairs still ray traced
 // (sel_list[n][kSelListCap], sel_n[n] = count or -1: left to launch_rt).
 constexpr int kSelListCap = 128;
+constexpr int kIncCap = 48; // incident tets of a node the walk can hold (more, or none: left to launch_rt)
 hipError_t launch_select(const DevMesh &m, const Thresholds &th, const LearnParams &lp, int precision, double *rtv,
                          int *sel_list, int *sel_n, float *sel_dmax, int *sel_cnt, hipStream_t s);
 // Walk variant (face-manifold meshes); nodes it cannot hold are appended to
@@ -138,10 +140,11 @@ hipError_t launch_select(const DevMesh &m, const Thresholds &th, const LearnPara
 // their rays meet after entering the mesh again.  With sel_n the ray-traced
 // tets come from launch_select, the walk adds to rtv and, for the nodes it
 // completes, adds sel_cnt[3 node + k] (pairs moved to G1, G4, G11) to the
-// counters.
+// counters.  nwave: workgroups per node (without n_reenter), each with partial
+// sums rtv[part][3][npad]; launch_rt and launch_select write part 0.
 hipError_t launch_rt_walk(const DevMesh &m, const Thresholds &th, const AngTab &ang, int all_pairs, float r_stop,
-                          unsigned long long *n_reenter, int precision, double *rtv, unsigned long long *cnt,
-                          int *fallback, int *n_fallback, const int *sel_list, const int *sel_n,
+                          unsigned long long *n_reenter, int nwave, int precision, double *rtv,
+                          unsigned long long *cnt, int *fallback, int *n_fallback, const int *sel_list, const int *sel_n,
                           const float *sel_dmax, const int *sel_cnt, hipStream_t s);
 // The boundary faces of the mesh, for rays that enter it from outside:
 // face[k] = (tet, f | 4 o): the face opposite the tet's vertex f, with p < q <
@@ -163,9 +166,11 @@ hipError_t launch_rt_reenter(const DevMesh &m, const Thresholds &th, const AngTa
 // order, FP64) instead.  tg: scratch of 10 doubles per tet.
 hipError_t launch_velocity_gradient(const DevMesh &m, const int *node_orig, const double *vel, double *tg,
                                     double *grad, const double *om, double *rate, hipStream_t s);
+// vel[node_orig[k]] (and vel2, if given) = the sum of the partials: far field
+// part[splits], band[nsplit], ray tracing rtv[nwave] (each [3][npad] or null).
 hipError_t launch_combine(const DevMesh &m, const int *node_orig, const double *part, int splits,
-                          const double *band, int nsplit, const double *rtv, double *vel, int *nonfinite,
-                          hipStream_t s);
+                          const double *band, int nsplit, const double *rtv, int nwave, double *vel, double *vel2,
+                          int *nonfinite, hipStream_t s);
 
 // Treecode far field (BS_FAR_TREECODE): the plan the host builds and the
 // per-evaluation moment buffers.  Clusters are numbered breadth first, so

@@ -1943,7 +1943,6 @@ __global__ void __launch_bounds__(64) k_rt(DevMesh m, Thresholds th, AngTab ang,
 // P_k+1) for the one k with [d, V, P_k] of sign s and [d, V, P_k+1] of sign
 // -s (the faces through V share those edges, so no two qualify; none does
 // only when the ray meets V itself, and the ray ends there).
-constexpr int kIncCap = 48;    // incident tets per node (more: left to k_rt)
 constexpr int kMaxSteps = 1 << 13; // tets per ray: bounds a walk that stalls on a degenerate crossing
 
 struct WalkLds {
@@ -2287,7 +2286,7 @@ __device__ __forceinline__ void sort_list(int *list, int n, int lane)
 // wrote the node's Gauss terms to rtv: the walk adds to them).
 template <int PREC, bool LISTED>
 __global__ void __launch_bounds__(64) k_rt_walk(DevMesh m, Thresholds th, AngTab ang, int all_pairs, float r_stop,
-                                                unsigned long long *__restrict__ n_reenter,
+                                                unsigned long long *__restrict__ n_reenter, int nwave,
                                                 double *__restrict__ rtv, unsigned long long *__restrict__ cnt,
                                                 int *__restrict__ fallback, int *__restrict__ n_fallback, const int *__restrict__ sel_list,
                                                 const int *__restrict__ sel_n, const float *__restrict__ sel_dmax,
@@ -2295,7 +2294,15 @@ __global__ void __launch_bounds__(64) k_rt_walk(DevMesh m, Thresholds th, AngTab
 {
     __shared__ typename std::conditional<LISTED, WalkLdsListed, WalkLds>::type W;
     const int lane = threadIdx.x;
-    const int self = blockIdx.x;
+    // nwave workgroups per node take its blocks of rays in turn, each with
+    // partial sums of its own (rtv[part]); the first one keeps the books
+    const int self = blockIdx.x / nwave, part = blockIdx.x - self * nwave;
+    rtv += (size_t)part * 3 * m.npad;
+    auto leave = [&]() { // the node goes to k_rt (partial sums of the others: none)
+        if (lane != 0) return;
+        if (part == 0) fallback[atomicAdd(n_fallback, 1)] = self;
+        else rtv[self] = rtv[m.npad + self] = rtv[2 * m.npad + self] = 0.0;
+    };
     float xhv[3], xlv[3], omx[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -2318,7 +2325,7 @@ __global__ void __launch_bounds__(64) k_rt_walk(DevMesh m, Thresholds th, AngTab
         if constexpr (LISTED) {
             nlist = sel_n[self];
             if (nlist < 0) {
-                if (lane == 0) fallback[atomicAdd(n_fallback, 1)] = self;
+                leave();
                 return;
             }
             for (int k0 = 0; k0 < nlist; k0 += 64) {
@@ -2383,7 +2390,7 @@ __global__ void __launch_bounds__(64) k_rt_walk(DevMesh m, Thresholds th, AngTab
     // a point that is no vertex of the mesh (inside a tet, or outside the
     // mesh) has no incident tet to start from: the candidate kernel takes it
     if (ninc > kIncCap || ninc == 0) {
-        if (lane == 0) fallback[atomicAdd(n_fallback, 1)] = self;
+        leave();
         return;
     }
     if (lane < ninc) {
@@ -2461,7 +2468,7 @@ __global__ void __launch_bounds__(64) k_rt_walk(DevMesh m, Thresholds th, AngTab
     // mesh before its stop distance (or starts outside) could enter it again
     // beyond; k_rt_reenter adds those parts of the node's rays
     bool early = false;
-    for (int bi = 0; bi < nblk; ++bi) {
+    for (int bi = part; bi < nblk; bi += nwave) {
         const int row = 8 * (bi / bcols) + (lane >> 3), col = 8 * (bi % bcols) + (lane & 7);
         const bool valid = row < ang.N && col < ang.M2;
         const int l = valid ? row * ang.M2 + col : 0;
@@ -2585,7 +2592,7 @@ __global__ void __launch_bounds__(64) k_rt_walk(DevMesh m, Thresholds th, AngTab
     const unsigned long long hits = wave_sum_u64(A.hits);
     const unsigned long long rts = wave_sum_u64((unsigned long long)A.retests);
     if (lane == 0) {
-        if (LISTED) {
+        if (LISTED && part == 0) {
             vx += rtv[self];
             vy += rtv[m.npad + self];
             vz += rtv[2 * m.npad + self];
@@ -2595,10 +2602,10 @@ __global__ void __launch_bounds__(64) k_rt_walk(DevMesh m, Thresholds th, AngTab
         rtv[2 * m.npad + self] = vz;
         if (cnt) {
             unsigned long long *c = cnt_copy(cnt, self);
-            atomicAdd(&c[2], A.pairs);
+            if (part == 0) atomicAdd(&c[2], A.pairs);
             atomicAdd(&c[3], hits);
             atomicAdd(&c[4], rts);
-            if (LISTED)
+            if (LISTED && part == 0)
                 for (int k = 0; k < 3; ++k) atomicAdd(&c[5 + k], (unsigned long long)sel_cnt[3 * (size_t)self + k]);
         }
     }
@@ -2942,14 +2949,15 @@ hipError_t launch_select(const DevMesh &m, const Thresholds &th, const LearnPara
 }
 
 hipError_t launch_rt_walk(const DevMesh &m, const Thresholds &th, const AngTab &ang, int all_pairs, float r_stop,
-                          unsigned long long *n_reenter, int precision, double *rtv, unsigned long long *cnt,
+                          unsigned long long *n_reenter, int nwave, int precision, double *rtv, unsigned long long *cnt,
                           int *fallback, int *n_fallback, const int *sel_list, const int *sel_n, const float *sel_dmax,
                           const int *sel_cnt, hipStream_t s)
 {
+    if (nwave < 1 || (nwave > 1 && n_reenter)) return hipErrorInvalidValue;
     if (m.n == 0) return hipSuccess;
     const bool L = sel_n != nullptr;
 #define BS_RW(P, LL)                                                                                               \
-    hipLaunchKernelGGL((k_rt_walk<P, LL>), dim3(m.n), dim3(64), 0, s, m, th, ang, all_pairs, r_stop, n_reenter, rtv, \
+    hipLaunchKernelGGL((k_rt_walk<P, LL>), dim3(m.n * nwave), dim3(64), 0, s, m, th, ang, all_pairs, r_stop, n_reenter, nwave, rtv, \
                        cnt, fallback, n_fallback, sel_list, sel_n, sel_dmax, sel_cnt)
     if (precision == 0) {
         if (L) BS_RW(0, true); else BS_RW(0, false);
@@ -2985,36 +2993,39 @@ hipError_t launch_rt_reenter(const DevMesh &m, const Thresholds &th, const AngTa
 }
 
 // ---------------------------------------------------------------------------
+// One thread per (component, node): the FP64 sum of the partials in a fixed
+// order, to the caller's array (input order) and, if vel2, a second one.
+// (One thread per node took 35 us where 1,331 nodes have 40 partials each.)
 __global__ void __launch_bounds__(256) k_combine(int n, int first, int npad, const int *__restrict__ node_orig,
                                                  const double *__restrict__ part, int splits,
                                                  const double *__restrict__ band, int nsplit,
-                                                 const double *__restrict__ rtv, double *__restrict__ vel,
-                                                 int *__restrict__ nonfinite)
+                                                 const double *__restrict__ rtv, int nwave, double *__restrict__ vel,
+                                                 double *__restrict__ vel2, int *__restrict__ nonfinite)
 {
-    const int k = blockIdx.x * 256 + threadIdx.x;
+    const int k = blockIdx.x * 256 + threadIdx.x, c = blockIdx.y;
     if (k >= n) return;
-    const int o = node_orig[k];
-    const int i = first + k;
-    bool bad = false;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        double v = 0.0;
-        for (int s = 0; s < splits; ++s) v += part[((size_t)s * 3 + c) * npad + i];
-        for (int s = 0; band && s < nsplit; ++s) v += band[((size_t)s * 3 + c) * npad + i];
-        if (rtv) v += rtv[(size_t)c * npad + i];
-        vel[3 * (size_t)o + c] = v;
-        bad |= !isfinite(v);
-    }
-    if (bad) atomicOr(nonfinite, 1);
+    const size_t i = (size_t)c * npad + first + k, step = (size_t)3 * npad;
+    double v = 0.0;
+#pragma unroll 8
+    for (int s = 0; s < splits; ++s) v += part[s * step + i];
+#pragma unroll 8
+    for (int s = 0; s < nsplit; ++s) v += band[s * step + i];
+#pragma unroll 4
+    for (int s = 0; s < nwave; ++s) v += rtv[s * step + i];
+    const size_t o = 3 * (size_t)node_orig[k] + c;
+    vel[o] = v;
+    if (vel2) vel2[o] = v;
+    if (!isfinite(v)) atomicOr(nonfinite, 1);
 }
 
 hipError_t launch_combine(const DevMesh &m, const int *node_orig, const double *part, int splits,
-                          const double *band, int nsplit, const double *rtv, double *vel, int *nonfinite,
-                          hipStream_t s)
+                          const double *band, int nsplit, const double *rtv, int nwave, double *vel, double *vel2,
+                          int *nonfinite, hipStream_t s)
 {
     if (m.n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_combine, dim3((m.n + 255) / 256), dim3(256), 0, s, m.n, m.blk0 * kBlockNodes, m.npad,
-                       node_orig, part, splits, band, nsplit, rtv, vel, nonfinite);
+    hipLaunchKernelGGL(k_combine, dim3((m.n + 255) / 256, 3), dim3(256), 0, s, m.n, m.blk0 * kBlockNodes, m.npad,
+                       node_orig, part, part ? splits : 0, band, band ? nsplit : 0, rtv, rtv ? nwave : 0, vel, vel2,
+                       nonfinite);
     return hipGetLastError();
 }
 
