@@ -2035,9 +2035,10 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, double *out2 = nullptr,
         // the walk on face-manifold meshes; where the boundary is not convex,
         // nodes with a ray that exits the mesh early take another pass for
         // the boundary faces through which it can enter again
-        if (m->manifold && m->rt_mode == 0 && !targets) {
+        // (points: the fixed rule inside a convex boundary)
+        if (m->manifold && m->rt_mode == 0 && (!targets || (m->convex && P.kind == BS_POLICY_FIXED))) {
             m->last_rt = 2;
-            if (!given && (rc = dalloc(m->fallback, 4 * (size_t)m->n))) return rc;
+            if (!given && (rc = dalloc(m->fallback, 4 * (size_t)std::max(m->n, m->tn)))) return rc;
             int *fb = given ? given->fallback : (int *)m->fallback.p;
             int *nfb = (int *)(cnt + 9);
             const float r_stop = all ? 3.0e38f : (float)((std::max(c_rt, m->max_vc) + m->max_vc) * (1.0 + 1e-4) + 1e-6);
@@ -2055,7 +2056,7 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, double *out2 = nullptr,
                                                    sel_cnt, sr))) ||
                 (e = bsk::launch_rt_walk(dm, th, ang, all, r_stop, m->convex ? nullptr : cnt + 8, nwave, P.precision, b_rtv,
                                          cnt, fb, nfb, sel_list, sel_n, sel_dmax, sel_cnt, sr)) ||
-                ((lp.net || !m->inc_walkable) &&
+                ((lp.net || !m->inc_walkable || targets) &&
                  (e = bsk::launch_rt(dm, th, ang, lp, all, P.precision, b_rtv, cnt, fb, nfb, sr))) ||
                 (!m->convex && (e = bsk::launch_rt_reenter(dm, th, ang,
                                                            {(const int2 *)m->bface.p, (const float4 *)m->bsph.p, m->nbface},

@@ -101,3 +101,42 @@ def test_rays_entering_the_mesh_again(kind, prec):
           f"rel-L2 {e:.3e}, worst node {worst:.3e}", flush=True)
     f = 1 if prec else 10
     assert e <= 1e-6 * f and worst <= 5e-6 * f, (e, worst)
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+def test_points_walk_from_their_tet(prec):
+    """Points (fixed rule, convex box): deep inside tets, within 1e-6 of
+    faces, edges and nodes, on them, and outside; those clear of every face
+    walk from the tet that holds them, the others take candidate rays.  The
+    oracle takes the points as nodes of no tet."""
+    m = W.make_config("C1", scale=(7, 8, 6))
+    rng = np.random.default_rng(2)
+    t = m.xyz[m.tets[rng.choice(m.n_tets, 240, replace=False)]]
+    lam = rng.dirichlet([2.0] * 4, size=240)
+    lam[60:120] = rng.dirichlet([1.0] * 3, size=60) @ np.eye(4)[:3]
+    lam[60:90, 3] = 1e-6
+    lam[120:150] = [0.3, 0.7, 0.0, 0.0]
+    lam[150:160] = [1.0, 0.0, 0.0, 0.0]
+    lam /= lam.sum(axis=1, keepdims=True)
+    pts = np.einsum("ij,ijk->ik", lam, t)
+    pts[220:] += np.array([2.5, 0.1, -0.2])  # outside
+    pts[90:120] += 1e-3 * rng.normal(size=(30, 3))
+    # (on a shared face, edge or node the chord's start is a tie: not compared)
+    keep = np.r_[0:90, 90:120, 160:240]
+    h = bs.bs_mesh_upload(m.xyz, m.omega, m.tets)
+    bs.bs_set_policy(h, kind=bs.BS_POLICY_FIXED, precision=prec)
+    v, st = bs.bs_eval_points(h, pts, stats=True)
+    bs.bs_mesh_free(h)
+    assert np.isfinite(v).all() and st["rt_walk_nodes"] > 100 and st["rt_candidate_nodes"] >= 20
+    xyz, om = np.concatenate([m.xyz, pts]), np.concatenate([m.omega, np.zeros_like(pts)])
+    ref, cnt = oracle.evaluate(xyz, om, m.tets, oracle.make_policy("fixed"),
+                               targets=np.arange(m.n_nodes, m.n_nodes + len(pts)), return_counters=True)
+    assert st["pairs_by_rule"] == cnt["pairs_by_rule"]
+    v, ref = v[keep], ref[keep]
+    scale = np.sqrt(np.mean(np.sum(ref * ref, axis=1)))
+    e = float(np.linalg.norm(v - ref) / np.linalg.norm(ref))
+    worst = float((np.linalg.norm(v - ref, axis=1) / np.maximum(np.linalg.norm(ref, axis=1), scale)).max())
+    print(f"  points precision {prec}: {st['rt_walk_nodes']} walked, {st['rt_candidate_nodes']} with candidate rays, "
+          f"rel-L2 {e:.3e}, worst {worst:.3e}", flush=True)
+    f = 1 if prec else 10
+    assert e <= 1e-6 * f and worst <= 5e-6 * f, (e, worst)
