@@ -111,7 +111,18 @@ constexpr int kCntStripes = 64;
 constexpr int kCntStride = 16; // 64-bit counters per copy (128 bytes)
 constexpr int kCntWords = kCntStripes * kCntStride;
 
+// Barycentric points and weights of the 1-, 4- and 11-point rules, in turn.
+struct GaussTables {
+    double lam[16][4], w[16];
+};
+
 // Launchers (return hipSuccess or the launch error).
+// Gauss records and vertex slots of every tet (position k: input tet
+// order[k]) from the FP64 node positions and vorticity (input order), and the
+// bits of the largest strength component (max_w, zero before).
+hipError_t launch_tet_records(int T, const int *order, const int4 *tets, const double *x64, const double *w64,
+                              const int *rank, const GaussTables &G, float *g1, float *g4, float *g11, int4 *tid,
+                              unsigned long long *max_w, hipStream_t s);
 hipError_t launch_gauss_all(const DevMesh &m, int rule_pts, int precision, int splits, double *part,
                             hipStream_t s);
 // Far field of the fixed-rule policies (G1 pairs only), precision 0 or 1.

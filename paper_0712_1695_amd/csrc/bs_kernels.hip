@@ -51,6 +51,80 @@ static_assert(sizeof(PackedNet) == kPackedNetBytes, "packed network layout");
 #define RULE_G11 2
 #define RULE_RT 3
 
+// One thread per tet: its Gauss points p = sum lam_j v_j and strengths
+// W = w |T| (sum lam_j omega_j) / 4 pi of the three rules, every operation in
+// FP64 without contraction, rounded to binary32 once.  The 1-point rule sits
+// at the centroid of the rule decision.  Bound by the 512 bytes a tet writes.
+__global__ void __launch_bounds__(256) k_tet_records(int T, const int *__restrict__ order,
+                                                     const int4 *__restrict__ tets, const double *__restrict__ x64,
+                                                     const double *__restrict__ w64, const int *__restrict__ rank,
+                                                     GaussTables G, float *__restrict__ g1, float *__restrict__ g4,
+                                                     float *__restrict__ g11, int4 *__restrict__ tid,
+                                                     unsigned long long *__restrict__ max_w)
+{
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    double mw = 0.0;
+    if (k < T) {
+        const int4 t4 = tets[order[k]];
+        const int id[4] = {t4.x, t4.y, t4.z, t4.w};
+        double v[4][3], w[4][3], e[3][3];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                v[j][c] = x64[3 * (size_t)id[j] + c];
+                w[j][c] = w64[3 * (size_t)id[j] + c];
+            }
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) e[j][c] = v[j + 1][c] - v[0][c];
+        const double det = e[0][0] * (e[1][1] * e[2][2] - e[1][2] * e[2][1]) -
+                           e[0][1] * (e[1][0] * e[2][2] - e[1][2] * e[2][0]) +
+                           e[0][2] * (e[1][0] * e[2][1] - e[1][1] * e[2][0]);
+        const double vol = fabs(det) / 6.0;
+        for (int q = 0; q < 16; ++q) {
+            double p[3] = {0.0, 0.0, 0.0}, o[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    p[c] += G.lam[q][j] * v[j][c];
+                    o[c] += G.lam[q][j] * w[j][c];
+                }
+            if (q == 0)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) p[c] = (((v[0][c] + v[1][c]) + v[2][c]) + v[3][c]) * 0.25;
+            const double f = G.w[q] * vol / (4.0 * M_PI);
+            float r[6];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                r[c] = (float)p[c];
+                r[3 + c] = (float)(f * o[c]);
+                mw = fmax(mw, fabs(f * o[c]));
+            }
+            float *d = q == 0 ? g1 + (size_t)k * kRecG
+                              : q < 5 ? g4 + ((size_t)k * 4 + (q - 1)) * kRecG : g11 + ((size_t)k * 11 + (q - 5)) * kRecG;
+            *reinterpret_cast<float4 *>(d) = make_float4(r[0], r[1], r[2], r[3]);
+            *reinterpret_cast<float4 *>(d + 4) = make_float4(r[4], r[5], 0.f, 0.f);
+        }
+        tid[k] = make_int4(rank[id[0]], rank[id[1]], rank[id[2]], rank[id[3]]);
+    }
+    for (int o = 32; o > 0; o >>= 1) mw = fmax(mw, __shfl_xor(mw, o, 64));
+    // (non-negative doubles order as their bits)
+    if ((threadIdx.x & 63) == 0 && mw > 0.0) atomicMax(max_w, (unsigned long long)__double_as_longlong(mw));
+}
+
+hipError_t launch_tet_records(int T, const int *order, const int4 *tets, const double *x64, const double *w64,
+                              const int *rank, const GaussTables &G, float *g1, float *g4, float *g11, int4 *tid,
+                              unsigned long long *max_w, hipStream_t s)
+{
+    if (T <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_tet_records, dim3((T + 255) / 256), dim3(256), 0, s, T, order, tets, x64, w64, rank, G, g1, g4,
+                       g11, tid, max_w);
+    return hipGetLastError();
+}
+
 // Fold a into the compensated pair (s, c) (Knuth's TwoSum).
 __device__ __forceinline__ void two_sum(float &s, float &c, float a)
 {
