@@ -237,7 +237,7 @@ def roof_entry(name, what, bound, kflops, t, workload, policy, precision, extra=
 
 def kernel_rooflines(st, kern, nm, workload, policy, precision, valu_far=False):
     g1, g4, g11, rtp = st["pairs_by_rule"]
-    far_name = "k_gauss_all" if (valu_far or precision == 2) else "k_far_mfma"
+    far_name = "k_gauss_all" if (valu_far or precision == 2) else "k_far_split"
     band_name = "k_band" if far_name == "k_gauss_all" else "k_band_piece"
     rt_what = ("learned selection pass and ray tracing by walking face neighbours; the method's flops of "
                "the ray-traced pairs" if policy == "learned"
@@ -245,7 +245,7 @@ def kernel_rooflines(st, kern, nm, workload, policy, precision, valu_far=False):
     rt_name = "k_select+k_rt_walk" if policy == "learned" else "k_rt_walk"
     return [
         roof_entry(far_name, "far field, 1-point rule on every pair, vector ALUs" if far_name == "k_gauss_all"
-                   else "far field, the G1 pairs, FP32 matrix-core contractions",
+                   else "far field, the G1 pairs, matrix-core contractions on 16-bit pieces, binary32 accuracy",
                    "alu" if far_name == "k_gauss_all" else "mfma", FLOPS_PER_POINT * g1, kern[0],
                    workload, policy, precision),
         roof_entry(band_name, "the G4 and G11 pairs, vector ALUs", "alu", FLOPS_PER_POINT * (4 * g4 + 11 * g11),
