@@ -205,13 +205,16 @@ __global__ void __launch_bounds__(256) k_tree_p2m(TreeView t)
     o[2] = mz;
 }
 
-__device__ __forceinline__ double binom(int n, int k)
-{
-    double r = 1.0;
-    for (int q = 1; q <= k; ++q) r = r * (double)(n - k + q) / (double)q;
-    return r;
-}
+// C(n, k) for n <= 6 (the orders are 2, 4 and 6).
+__constant__ double kBinom[7][7] = {{1, 0, 0, 0, 0, 0, 0},  {1, 1, 0, 0, 0, 0, 0},   {1, 2, 1, 0, 0, 0, 0},
+                                    {1, 3, 3, 1, 0, 0, 0},  {1, 4, 6, 4, 1, 0, 0},   {1, 5, 10, 10, 5, 1, 0},
+                                    {1, 6, 15, 20, 15, 6, 1}};
 
+// One thread per coefficient of a cluster of one level.  The levels run one
+// after the other and most hold few clusters, so the time is one thread's
+// chain: binomials from a table and powers by one multiplication per step.
+// (Each term's three binomials by divisions and powers by loops took 137 us
+// level at order 6, M2MLEVEL so; 15 levels on the ring mesh.)
 template <int P>
 __global__ void __launch_bounds__(256) k_tree_m2m(TreeView t, int node0, int node1)
 {
@@ -230,16 +233,22 @@ __global__ void __launch_bounds__(256) k_tree_m2m(TreeView t, int node0, int nod
         const double dx = t.c64[4 * c] - t.c64[4 * j], dy = t.c64[4 * c + 1] - t.c64[4 * j + 1],
                      dz = t.c64[4 * c + 2] - t.c64[4 * j + 2];
         const double *Mc = t.M + (size_t)c * NK * 3;
-        for (int a = 0; a <= ei; ++a)
-            for (int b = 0; b <= ej; ++b)
-                for (int e = 0; e <= el; ++e) {
-                    const double f = binom(ei, a) * binom(ej, b) * binom(el, e) * ipow(dx, ei - a) *
-                                     ipow(dy, ej - b) * ipow(dz, el - e);
+        double pa = 1.0; // dx^(ei - a)
+        for (int a = ei; a >= 0; --a, pa *= dx) {
+            const double fa = kBinom[ei][a] * pa;
+            double pb = 1.0;
+            for (int b = ej; b >= 0; --b, pb *= dy) {
+                const double fb = fa * (kBinom[ej][b] * pb);
+                double pe = 1.0;
+                for (int e = el; e >= 0; --e, pe *= dz) {
+                    const double f = fb * (kBinom[el][e] * pe);
                     const double *m = Mc + 3 * tc_index(a, b, e);
                     mx += f * m[0];
                     my += f * m[1];
                     mz += f * m[2];
                 }
+            }
+        }
     }
     double *o = t.M + ((size_t)j * NK + k) * 3;
     o[0] = mx;
