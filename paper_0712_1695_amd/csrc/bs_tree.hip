@@ -214,7 +214,7 @@ __constant__ double kBinom[7][7] = {{1, 0, 0, 0, 0, 0, 0},  {1, 1, 0, 0, 0, 0, 0
 // after the other and most hold few clusters, so the time is one thread's
 // chain: binomials from a table and powers by one multiplication per step.
 // (Each term's three binomials by divisions and powers by loops took 137 us
-// level at order 6, M2MLEVEL so; 15 levels on the ring mesh.)
+// per level at order 6, this 44; 15 levels on the ring mesh.)
 template <int P>
 __global__ void __launch_bounds__(256) k_tree_m2m(TreeView t, int node0, int node1)
 {
