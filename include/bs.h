@@ -205,7 +205,9 @@ typedef struct {
     int64_t rt_walk_nodes;    /* nodes ray traced by walking face neighbours   */
     int64_t rt_candidate_nodes; /* nodes with candidate rays tested, per pair:
                                  * off-node points, nodes with no or more than
-                                 * 48 incident tets; or per boundary face, for
+                                 * 48 incident tets, nodes inside or on a tet
+                                 * they are no vertex of (parts that touch or
+                                 * overlap); or per boundary face, for
                                  * rays entering the mesh again: where the
                                  * boundary is not convex, nodes with a ray
                                  * that leaves the mesh before its last

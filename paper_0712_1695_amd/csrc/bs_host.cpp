@@ -284,14 +284,17 @@ struct bs_mesh {
     std::vector<int32_t> nbr_in;  // [T][4] face neighbours (input tet numbering, -1 boundary)
     std::vector<int32_t> inc_in_start, inc_in_list; // corners 4t + j of every input node, by node (built once)
     std::vector<int64_t> edge_keys; // unique edges, sorted (lo * (n + 1) + hi); built on first use
-    DBuf x64, tord, slots, tin, maxw; // inputs of the record kernel (FP64 positions, tet order, node slots, connectivity); max_w's bits
+    DBuf x64, tord, slots, tin; // inputs of the record kernel (FP64 positions, tet order, node slots, connectivity)
+    DBuf found; // what the kernels of a build find: max_w's bits, nheld
     bool manifold = true;         // every face shared by at most two tets
     bool convex = false;          // boundary is one closed, locally convex surface (rays never re-enter)
     bsk::Bins bins{};
     // device buffers
     DBuf tsph; // bounding spheres of 16-tet tiles
     DBuf xh, xl, om, nrec, blk, node_orig, g1, g4, g11, tid, cell_start, nbr, inc_start, inc_list, bface, bsph;
-    bool inc_walkable = false;       // every node has 1 .. kIncCap incident tets (the walk leaves none to k_rt)
+    bool inc_walkable = false;       // every node has 1 .. kIncCap incident tets
+    DBuf held;                       // nodes in or on a tet they are not a vertex of (boundary not convex)
+    unsigned long long nheld = 0;    // how many (the walk leaves them to k_rt)
     int nbface = 0;                  // boundary faces in bface (0 where the boundary is convex)
     std::vector<int64_t> bface_in;   // 4 * tet + face of every boundary face, input numbering
     DBuf part, band, rtv, vel, cnt, fallback;
@@ -1007,6 +1010,8 @@ struct JoinedThread {
     ~JoinedThread() { join(); }
 };
 
+bsk::DevMesh dev_view(const bs_mesh *m);
+
 int build_device_mesh(bs_mesh *m, hipStream_t s)
 {
     int rc;
@@ -1174,7 +1179,8 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
     if ((rc = dalloc(m->g1, 4 * (size_t)T * 8)) || (rc = dalloc(m->g4, 4 * (size_t)T * 32)) ||
         (rc = dalloc(m->g11, 4 * (size_t)T * 88)) || (rc = dalloc(m->tid, sizeof(int4) * (size_t)T)) ||
         (rc = dalloc(m->om64, 8 * 3 * (size_t)std::max<int64_t>(n, 1))) || (rc = dalloc(m->x64, 8 * 3 * (size_t)n)) ||
-        (rc = dalloc(m->tord, 4 * (size_t)T)) || (rc = dalloc(m->slots, 4 * (size_t)n)) || (rc = dalloc(m->maxw, 8)))
+        (rc = dalloc(m->tord, 4 * (size_t)T)) || (rc = dalloc(m->slots, 4 * (size_t)n)) || (rc = dalloc(m->found, 16)) ||
+        (rc = dalloc(m->held, (size_t)n)) || (rc = dalloc(m->cell_start, 4 * cell_start.size())))
         return rc;
     const bool have_tin = m->tin.p != nullptr;
     if (!have_tin && (rc = dalloc(m->tin, sizeof(int4) * (size_t)T))) return rc;
@@ -1187,8 +1193,9 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
         up(m->x64, X, 8 * 3 * (size_t)n);
         up(m->tord, order.data(), 4 * (size_t)T);
         up(m->slots, rank.data(), 4 * (size_t)n);
+        up(m->cell_start, cell_start.data(), 4 * cell_start.size());
         if (!have_tin) up(m->tin, m->tets.data(), sizeof(int4) * (size_t)T);
-        if (e == hipSuccess) e = hipMemsetAsync(m->maxw.p, 0, 8, s);
+        if (e == hipSuccess) e = hipMemsetAsync(m->found.p, 0, 16, s);
         bsk::GaussTables G{};
         int q = 0;
         for (int pts : {1, 4, 11}) {
@@ -1202,17 +1209,28 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
             e = bsk::launch_tet_records((int)T, (const int *)m->tord.p, (const int4 *)m->tin.p, (const double *)m->x64.p,
                                         (const double *)m->om64.p, (const int *)m->slots.p, G, (float *)m->g1.p,
                                         (float *)m->g4.p, (float *)m->g11.p, (int4 *)m->tid.p,
-                                        (unsigned long long *)m->maxw.p, s);
+                                        (unsigned long long *)m->found.p, s);
         if (e != hipSuccess) {
             (void)hipStreamSynchronize(s);
             if (!have_tin) dfree(m->tin); // (not known to hold the connectivity)
             return hip_fail(e, "Gauss records");
         }
     }
+    // nodes in or on other tets: where the boundary is not convex, known only
+    // at the end (so already now unless it was convex the last time)
+    auto find_held = [&]() -> int {
+        const float reach = (float)(max_vc * (1.0 + 1e-4) + 16.0 * std::ldexp(1.0, -24) * max_abs);
+        const hipError_t e = bsk::launch_nodes_held(
+            dev_view(m), (const double *)m->x64.p, (const int *)m->tord.p, (const int4 *)m->tin.p,
+            (const int *)m->slots.p, reach, (unsigned char *)m->held.p, (unsigned long long *)m->found.p + 1, s);
+        return e == hipSuccess ? BS_OK : hip_fail(e, "nodes inside other tets");
+    };
     auto wait_records = [&](int r) {
         (void)hipStreamSynchronize(s);
         return r;
     };
+    const bool held_known = T > 0 && m->manifold && !m->convex; // (m->convex: of the last build)
+    if (held_known && (rc = find_held())) return wait_records(rc);
 
     // ---- bounding sphere of the binary32 centroids of every tile of 16
     // consecutive (sorted) tets, for the far kernel's band flags
@@ -1332,7 +1350,6 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
         (rc = dalloc(m->blk, sizeof(float4) * blk.size())) || (rc = dalloc(m->node_orig, 4 * (size_t)n)) ||
         (rc = dalloc(m->torig, 4 * torig.size())) || (rc = dalloc(m->tlist, 4 * tlist.size())) ||
         (rc = dalloc(m->tvel, 8 * 3 * (size_t)tn)) ||
-        (rc = dalloc(m->cell_start, 4 * cell_start.size())) ||
         (rc = dalloc(m->vel, 8 * 3 * (size_t)n)) ||
         (rc = dalloc(m->cnt, 8 * bsk::kCntWords)) ||
         (rc = dalloc(m->nbr, sizeof(int4) * (size_t)T)) ||
@@ -1355,7 +1372,6 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
     BS_UP(node_orig, orig)
     BS_UP(torig, torig)
     BS_UP(tlist, tlist)
-    BS_UP(cell_start, cell_start)
     BS_UP(nbr, nbr)
     BS_UP(tsph, tsph)
     BS_UP(inc_start, inc_start)
@@ -1363,10 +1379,14 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
     BS_UP(bface, bface)
     BS_UP(bsph, bsph)
 #undef BS_UP
-    if ((e = hipMemcpyAsync(&m->max_w, m->maxw.p, 8, hipMemcpyDeviceToHost, s)) != hipSuccess)
+    if (m->nbface > 0 && !held_known && (rc = find_held())) return wait_records(rc);
+    unsigned long long found[2] = {0, 0};
+    if ((e = hipMemcpyAsync(found, m->found.p, 16, hipMemcpyDeviceToHost, s)) != hipSuccess)
         return wait_records(hip_fail(e, "upload"));
     e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "upload");
+    std::memcpy(&m->max_w, &found[0], 8);
+    m->nheld = m->nbface > 0 ? found[1] : 0;
     if (uses_treecode(m->pol) && (rc = build_tree_plan(m, s))) return rc;
     return BS_OK;
 }
@@ -1700,7 +1720,7 @@ void bs_mesh_free(bs_mesh *m)
                     &m->tree.nrange, &m->tree.child, &m->tree.leaves, &m->tree.c64, &m->tree.crec,
                     &m->tree.src64, &m->tree.g1t, &m->tree.tidt, &m->tree.M, &m->tree.N, &m->tree.acc_start,
                     &m->tree.acc, &m->tree.dir_start, &m->tree.dir, &m->tree.torder, &m->tree.tin, &m->tree.x64,
-                    &m->tree.rank, &m->x64, &m->tord, &m->slots, &m->tin, &m->maxw};
+                    &m->tree.rank, &m->x64, &m->tord, &m->slots, &m->tin, &m->found, &m->held};
     for (DBuf *b : bufs) dfree(*b);
     for (auto &a : m->aux)
         if (a) (void)hipStreamSynchronize(a);
@@ -1994,8 +2014,9 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, double *out2 = nullptr,
             if ((lp.net && (e = bsk::launch_select(dm, th, lp, P.precision, b_rtv, sel_list, sel_n, sel_dmax,
                                                    sel_cnt, sr))) ||
                 (e = bsk::launch_rt_walk(dm, th, ang, all, r_stop, m->convex ? nullptr : cnt + 8, nwave, P.precision, b_rtv,
-                                         cnt, fb, nfb, sel_list, sel_n, sel_dmax, sel_cnt, sr)) ||
-                ((lp.net || !m->inc_walkable || targets) &&
+                                         cnt, fb, nfb, sel_list, sel_n, sel_dmax, sel_cnt,
+                                         m->nheld > 0 ? (const unsigned char *)m->held.p : nullptr, sr)) ||
+                ((lp.net || !m->inc_walkable || m->nheld > 0 || targets) &&
                  (e = bsk::launch_rt(dm, th, ang, lp, all, P.precision, b_rtv, cnt, fb, nfb, sr))) ||
                 (!m->convex && (e = bsk::launch_rt_reenter(dm, th, ang,
                                                            {(const int2 *)m->bface.p, (const float4 *)m->bsph.p, m->nbface},

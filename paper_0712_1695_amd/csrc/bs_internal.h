@@ -151,12 +151,20 @@ hipError_t launch_select(const DevMesh &m, const Thresholds &th, const LearnPara
 // their rays meet after entering the mesh again.  With sel_n the ray-traced
 // tets come from launch_select, the walk adds to rtv and, for the nodes it
 // completes, adds sel_cnt[3 node + k] (pairs moved to G1, G4, G11) to the
-// counters.  nwave: workgroups per node (without n_reenter), each with partial
+// counters.  held (null: none): nodes of launch_nodes_held, left to launch_rt.
+// nwave: workgroups per node (without n_reenter), each with partial
 // sums rtv[part][3][npad]; launch_rt and launch_select write part 0.
 hipError_t launch_rt_walk(const DevMesh &m, const Thresholds &th, const AngTab &ang, int all_pairs, float r_stop,
                           unsigned long long *n_reenter, int nwave, int precision, double *rtv,
                           unsigned long long *cnt, int *fallback, int *n_fallback, const int *sel_list, const int *sel_n,
-                          const float *sel_dmax, const int *sel_cnt, hipStream_t s);
+                          const float *sel_dmax, const int *sel_cnt, const unsigned char *held,
+                          hipStream_t s);
+// held[slot] = 1 for the nodes in or on a tet they are not a vertex of, 0 for
+// the others; *count += their number.  Inputs as launch_tet_records, with the
+// bins, cell_start and g1 of m; reach: no less than any vertex's distance from
+// its tet's centroid, with the rounding of the coordinates.
+hipError_t launch_nodes_held(const DevMesh &m, const double *x64, const int *order, const int4 *tets, const int *rank,
+                             float reach, unsigned char *held, unsigned long long *count, hipStream_t s);
 // The boundary faces of the mesh, for rays that enter it from outside:
 // face[k] = (tet, f | 4 o): the face opposite the tet's vertex f, with p < q <
 // r its vertices in local order; o = 0 if [p - x, q - x, r - x] is positive

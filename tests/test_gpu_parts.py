@@ -1,0 +1,123 @@
+"""Ray tracing on meshes whose parts touch or overlap with nodes of their own,
+and on slits with doubled nodes: a ray from a node in or on a tet it is no
+vertex of begins inside that tet, without crossing its boundary from outside.
+
+A cut mesh has the velocities of the mesh it was cut from (the same tets), so
+the two are compared with each other; the FP64 oracle, whose tie rule drops
+chords that start exactly on a face, is the reference where no node lies on
+another part.  Tolerance: relative L2 1e-6 of each side, so 2e-6 between two
+meshes; the cut mesh's distances in units of its own mean edge length are
+scaled to the joined one's.  A dropped part of one ray is 1e-3 or more."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_0712_1695_amd as bs
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+CUTS = dict(near_cut=2.0, d_g11=4.0, d_g4=8.0)
+
+
+def policy(kind, scale=1.0):
+    if kind == "pure":
+        return dict(kind=bs.BS_POLICY_PURE_RT, n_phi=8, n_theta=8)
+    cuts = {k: v * scale for k, v in CUTS.items()}
+    if kind == "fixed":
+        return dict(kind=bs.BS_POLICY_FIXED, **cuts)
+    # a network of zeros gives every class the probability 1/4: at 0.8 no
+    # Gauss rule is sure enough and every pair stays ray traced
+    return dict(kind=bs.BS_POLICY_LEARNED, mlp_bf16=np.zeros(5540, np.uint16), conf_min=0.8, **cuts)
+
+
+def evaluate(xyz, om, tets, kind, hbar=None):
+    h = bs.bs_mesh_upload(xyz, om, tets)
+    bs.bs_set_policy(h, **policy("pure"))
+    hb = bs.bs_eval_velocity(h, stats=True)[1]["hbar"]
+    bs.bs_set_policy(h, **policy(kind, 1.0 if hbar is None else hbar / hb))
+    v, st = bs.bs_eval_velocity(h, stats=True)
+    bs.bs_mesh_free(h)
+    return v, st
+
+
+def rel(v, ref):
+    return float(np.linalg.norm(v - ref) / np.linalg.norm(ref))
+
+
+def joined():
+    m = W.make_config("C1", scale=(6, 6, 6))
+    return m.xyz, m.omega + np.array([0.05, 0.1, -0.03]), m.tets
+
+
+def doubled(xyz, om, tets, side, nodes):
+    """The tets of `side` get copies of the given nodes.  Returns the mesh and
+    the node each new node comes from."""
+    new = {int(k): len(xyz) + i for i, k in enumerate(nodes)}
+    t = tets.copy()
+    t[side] = [[new.get(int(v), int(v)) for v in row] for row in tets[side]]
+    src = np.concatenate([np.arange(len(xyz)), np.asarray(nodes)])
+    return xyz[src], om[src], t, src
+
+
+@pytest.mark.parametrize("kind,shift", [("pure", 0.0), ("fixed", 0.0), ("learned", 0.0), ("pure", 100.0)])
+@pytest.mark.parametrize("cut", ["parts", "slit"])
+def test_doubled_nodes(kind, cut, shift):
+    """A box cut at x = 0 into two parts, or half way (a slit)."""
+    xyz, om, tets = joined()
+    i, j = np.arange(343) % 7, (np.arange(343) // 7) % 7
+    nodes = np.nonzero((i == 3) & ((j < 3) | (cut == "parts")))[0]
+    x, o, t, src = doubled(xyz + shift, om, tets, i[tets].max(axis=1) > 3, nodes)
+    ref, s0 = evaluate(xyz + shift, om, tets, kind)
+    v, s1 = evaluate(x, o, t, kind, s0["hbar"])
+    e = rel(v, ref[src])
+    worst = np.linalg.norm(v - ref[src], axis=1).max() / np.sqrt((ref * ref).sum(axis=1).mean())
+    print(f"  {cut} {kind}: rel-L2 {e:.2e}, worst {worst:.2e}, {s1['rt_candidate_nodes']} candidate nodes", flush=True)
+    assert e <= 2e-6 and worst <= 1e-4, (e, worst)
+
+
+def box(lo, hi, cells, seed):
+    xyz, tets, h, b = W.kuhn_grid(lo, hi, cells)
+    xyz = W.jitter_interior(xyz, b, h, 0.1, seed)
+    return xyz, W.orient_positive(xyz, tets)
+
+
+@pytest.mark.parametrize("kind", ["pure", "fixed"])
+@pytest.mark.parametrize("other", ["overlapping", "gap"])
+def test_two_boxes_against_the_oracle(kind, other):
+    """Two boxes meshed on their own, overlapping (the velocity of the sum of
+    both) or 1e-9 apart.  No node of one is on a face of the other."""
+    a = box((-1, -1, -1), (0, 1, 1), (3, 6, 6), 1)
+    b = box((-0.4, -0.6, -0.5), (1, 0.7, 1.3), (4, 5, 7), 2) if other == "overlapping" else \
+        box((1e-9, -1, -1), (1, 1, 1), (4, 5, 7), 2)
+    xyz, tets = np.concatenate([a[0], b[0]]), np.concatenate([a[1], b[1] + len(a[0])]).astype(np.int32)
+    om = W.field_gaussian_swirl(xyz) + np.array([0.05, 0.1, -0.03])
+    v, st = evaluate(xyz, om, tets, kind)
+    pol = oracle.make_policy("pure_rt", n_phi=8, n_theta=8) if kind == "pure" else oracle.make_policy("fixed")
+    ref, cnt = oracle.evaluate(xyz, om, tets, pol, return_counters=True)
+    e = rel(v, ref)
+    print(f"  {other} {kind}: rel-L2 {e:.2e}, {st['rt_candidate_nodes']} candidate nodes", flush=True)
+    assert st["pairs_by_rule"] == cnt["pairs_by_rule"]
+    assert e <= 1e-6, e
+
+
+@pytest.mark.parametrize("kind", ["pure", "fixed"])
+def test_parts_that_do_not_match(kind):
+    """Two boxes with different grids on their common face: at the nodes off
+    that face the oracle's velocities, at the nodes on it those of the same
+    boxes 1e-9 apart, where no ray starts on a face."""
+    def mesh(gap):
+        a, b = box((-1, -1, -1), (0, 1, 1), (3, 6, 6), 1), box((gap, -1, -1), (1, 1, 1), (4, 5, 7), 2)
+        return np.concatenate([a[0], b[0]]), np.concatenate([a[1], b[1] + len(a[0])]).astype(np.int32)
+
+    xyz, tets = mesh(0.0)
+    om = W.field_gaussian_swirl(xyz) + np.array([0.05, 0.1, -0.03])
+    v, _ = evaluate(xyz, om, tets, kind)
+    pol = oracle.make_policy("pure_rt", n_phi=8, n_theta=8) if kind == "pure" else oracle.make_policy("fixed")
+    ref = oracle.evaluate(xyz, om, tets, pol)
+    on = xyz[:, 0] == 0.0
+    ref[on] = oracle.evaluate(mesh(1e-9)[0], om, tets, pol, targets=np.nonzero(on)[0])
+    e = rel(v, ref)
+    print(f"  {kind}: rel-L2 {e:.2e}", flush=True)
+    # (rays along the common face may go to either part: 1e-6 at the others)
+    assert e <= 1e-3 and rel(v[~on], ref[~on]) <= 1e-6, (e, rel(v[~on], ref[~on]))
