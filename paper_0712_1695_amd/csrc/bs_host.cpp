@@ -286,7 +286,7 @@ struct bs_mesh {
     std::vector<int64_t> edge_keys; // unique edges, sorted (lo * (n + 1) + hi); built on first use
     DBuf x64, tord, slots, tin; // inputs of the record kernel (FP64 positions, tet order, node slots, connectivity)
     DBuf found; // what the kernels of a build find: max_w's bits, nheld
-    bool manifold = true;         // every face shared by at most two tets
+    bool manifold = true;         // every face shared by at most two tets, one on each side
     bool convex = false;          // boundary is one closed, locally convex surface (rays never re-enter)
     bsk::Bins bins{};
     // device buffers
@@ -487,8 +487,24 @@ int validate_geometry(bs_mesh *m)
     return BS_OK;
 }
 
+// Side of the face opposite local vertex f of tet t (its nodes in increasing
+// order) on which the tet lies.
+int face_side(const bs_mesh *m, int64_t tf)
+{
+    const int64_t t = tf / 4;
+    const int f = (int)(tf & 3);
+    int32_t v[3], k = 0;
+    for (int j = 0; j < 4; ++j)
+        if (j != f) v[k++] = m->tets[(size_t)(4 * t + j)];
+    const bool odd = (v[0] > v[1]) ^ (v[0] > v[2]) ^ (v[1] > v[2]);
+    return m->orient[(size_t)t] * ((f & 1) ? -1 : 1) * (odd ? -1 : 1);
+}
+
 // Face neighbours of every tet (input numbering): the face opposite local
-// vertex f of tet t is keyed by its sorted node triple.
+// vertex f of tet t is keyed by its sorted node triple.  A mesh in which a
+// face has both its tets on one side (folded over it: a ray leaves both
+// through it) is not manifold for the walk either; moving the nodes does not
+// change that, as no tet may invert.
 void build_neighbours(bs_mesh *m)
 {
     const int64_t T = m->T;
@@ -532,6 +548,7 @@ void build_neighbours(bs_mesh *m)
         if (j - i == 2) {
             m->nbr_in[(size_t)fk[i].tf] = (int32_t)(fk[i + 1].tf / 4);
             m->nbr_in[(size_t)fk[i + 1].tf] = (int32_t)(fk[i].tf / 4);
+            if (face_side(m, fk[i].tf) == face_side(m, fk[i + 1].tf)) m->manifold = false;
         } else if (j - i > 2) {
             m->manifold = false;
         }

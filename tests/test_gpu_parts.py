@@ -121,3 +121,38 @@ def test_parts_that_do_not_match(kind):
     print(f"  {kind}: rel-L2 {e:.2e}", flush=True)
     # (rays along the common face may go to either part: 1e-6 at the others)
     assert e <= 1e-3 and rel(v[~on], ref[~on]) <= 1e-6, (e, rel(v[~on], ref[~on]))
+
+
+def folded(notch):
+    """A box whose interior nodes are moved so far that some tets invert: two
+    tets on the same side of a face they share."""
+    grid, tets, h, b = W.kuhn_grid((-1, -1, -1), (1, 1, 1), (6, 6, 6))
+    xyz = W.jitter_interior(grid, b, h, 0.62, 5)
+    c = grid[tets].mean(axis=1)
+    if notch:
+        tets = np.ascontiguousarray(tets[~((c[:, 0] > 0) & (c[:, 1] > 0))])
+    v = W.signed_volumes6(xyz, tets)
+    assert (v < 0).any() and (v > 0).any()
+    return xyz, W.field_gaussian_swirl(xyz) + np.array([0.05, 0.1, -0.03]), tets
+
+
+@pytest.mark.parametrize("notch", [False, True])
+@pytest.mark.parametrize("kind", ["pure", "fixed", "points"])
+def test_folded_faces(kind, notch):
+    """Every pair is its own integral, so a folded mesh has the velocities of
+    the sum over its tets, at its nodes and at points."""
+    xyz, om, tets = folded(notch)
+    pol = oracle.make_policy("pure_rt", n_phi=8, n_theta=8) if kind == "pure" else oracle.make_policy("fixed")
+    if kind == "points":
+        pts = np.random.default_rng(3).uniform(-0.9, 0.9, size=(200, 3))
+        h = bs.bs_mesh_upload(xyz, om, tets)
+        bs.bs_set_policy(h, **policy("fixed"))
+        v = bs.bs_eval_points(h, pts)
+        bs.bs_mesh_free(h)
+        ref = oracle.evaluate(np.concatenate([xyz, pts]), np.concatenate([om, 0 * pts]), tets, pol,
+                              targets=np.arange(len(xyz), len(xyz) + 200))
+    else:
+        v, _ = evaluate(xyz, om, tets, kind)
+        ref = oracle.evaluate(xyz, om, tets, pol)
+    print(f"  {kind} notch {notch}: rel-L2 {rel(v, ref):.2e}", flush=True)
+    assert rel(v, ref) <= 1e-6, rel(v, ref)
