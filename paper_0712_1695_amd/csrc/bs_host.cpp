@@ -1850,15 +1850,17 @@ struct EvalBufs {
 // Scales of the split contraction (bs_split_dev.h) for pairs no closer than
 // `cut`, whose scaled distance is at least 2^-5, so that d^-3 <= 2^15, and
 // for strengths times offsets up to 2^15: both fit binary16.  eps: relative
-// margin on d^2 around the cut.  Its low pieces lose bits below 2^-24, which
-// is 2^-36 of the largest d^-3 or less; out to 128 cuts (d^-3 down to 2^-21
-// of the largest) a pair's loss stays below 2^-13 of the rounding error of
-// one pair at the cut.  Larger extents, vanishing cuts and strengths outside
-// binary32's normal range keep the binary32 contraction (xs = 0).
+// margin on d^2 around the cut.  A binary16 pair holds 23 bits of a value of
+// at least 2^-3; d^-3 stays above that out to 32 cuts (scaled distances up to
+// 2), whatever pairs a target has.  (At 64 cuts a target with no pair near the
+// cut would lose up to 3 bits, at 128 cuts 6: its velocity's relative error
+// grew 1e-7 -> 7e-7 -> 4e-6 on six tets; the binary32 contraction stays at
+// 1e-7.)  Larger extents, vanishing cuts and strengths that do not fit keep
+// the binary32 contraction (xs = 0).
 void split_scales(const bs_mesh *m, double cut, double eps, bsk::Thresholds &th)
 {
     th.xs = th.ws = th.d2_g1 = th.d2_amb = 0.f;
-    if (!(cut > 1e-12) || !(cut < 1e12) || !(eps < 0.5) || !(m->extent <= 128.0 * cut) || !(m->max_w < 1e25)) return;
+    if (!(cut > 1e-12) || !(cut < 1e12) || !(eps < 0.5) || !(m->extent <= 32.0 * cut) || !(m->max_w < 1e25)) return;
     int k = 0;
     std::frexp(cut, &k); // cut in [2^(k-1), 2^k)
     const double xs = std::ldexp(1.0, -k - 4);

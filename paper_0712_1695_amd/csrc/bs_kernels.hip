@@ -714,18 +714,22 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
 // every mesh and policy whose distances and strengths fit its number range
 // (Thresholds::xs, set on the host).  Workgroup, splits, chunks, prefetch and
 // band flags as in k_far_mfma; a wave takes units of 32 tets (two per chunk)
-// against the block's four node tiles, and its binary32 sums are folded into
-// the workgroup's compensated sums every fourth chunk (16 accumulations), the
-// waves in turn.  Two-ring mesh (531,441 nodes, 3,072,000 tets): 412 ms
-// against k_far_mfma's 508.  Bound by issue: per 1024 pairs and SIMD about
-// 390 cycles of vector instructions for the cubes and their pieces, 192 of
-// MFMA, 110 for preparing the operands, partly overlapped (635 in all).
-// Relative L2 error against the FP64 oracle (fixed rule, all kernels;
-// k_far_mfma in brackets): ring 6.5e-8 (6.7e-8), two rings 5.8e-8 (6.0e-8),
-// Fourier field 8.7e-8 (8.6e-8).  Measured and left: five waves per SIMD
+// against the block's four node tiles; a unit's sums are added in binary32 and
+// folded into the workgroup's compensated sums every fourth chunk (eight
+// additions), the waves in turn.  Two-ring mesh (531,441 nodes, 3,072,000
+// tets): 428 ms against k_far_mfma's 508.  Bound by issue: per 1024 pairs and
+// SIMD about 390 cycles of vector instructions for the cubes and their pieces,
+// 30 for the sums, 192 of MFMA, 110 for preparing the operands, partly
+// overlapped (660 in all).  Relative L2 error against the FP64 oracle (fixed
+// rule, all kernels; k_far_mfma in brackets): ring 6.50e-8 (6.71e-8), two
+// rings 5.78e-8 (6.01e-8), Fourier field 8.69e-8 (8.63e-8), swirl 4.94e-8
+// (4.94e-8); 2,058 tets seen from 4 to 30 cuts away 2.1 to 4.4e-8 (2.4 to
+// 2.8e-8).  (Accumulated by the instruction itself: 412 ms, but 5.81e-8,
+// 8.74e-8 and 3.5 to 5.3e-8.)  Measured and left: five waves per SIMD
 // (96 registers, spilled: +14%), raised wave priority at the MFMAs (+1%), two
 // blocks per workgroup around a common centre (spilled: +46%), the distances
-// on v_mfma_f32_16x16x4f32 (+5%).
+// on v_mfma_f32_16x16x4f32 (+5%), folding every chunk (+13%, ring 0.1% less
+// error).
 struct FarSplitLds {
     SplitUnit u[2][kFarChunk / 32];
     unsigned band[2][16];      // [buf][tile]: bit nt = within the band of node tile nt
@@ -883,8 +887,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
                 }
                 f16x8 h, l;
                 split_cubes(iv, h, l);
-                D[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A2, h, D[nt], 0, 0, 0);
-                D[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A2, l, D[nt], 0, 0, 0);
+                // the unit's sum on its own, added in binary32: the instruction
+                // rounds four times at the magnitude of what it adds to
+                // (the empty statement keeps the addition here; the compiler
+                // would put off all four tiles' to the end of the unit and
+                // spill)
+                f32x4 t = {0.f, 0.f, 0.f, 0.f};
+                t = __builtin_amdgcn_mfma_f32_16x16x32_f16(A2, l, t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_16x16x32_f16(A2, h, t, 0, 0, 0);
+                D[nt] = D[nt] + t;
+                asm volatile("" : "+v"(D[nt]));
             }
         }
         if (PREC == 1 && (k & 3) == wave) fold();
