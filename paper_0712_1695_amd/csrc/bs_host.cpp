@@ -1855,16 +1855,17 @@ struct EvalBufs {
 // 2), whatever pairs a target has.  (At 64 cuts a target with no pair near the
 // cut would lose up to 3 bits, at 128 cuts 6: its velocity's relative error
 // grew 1e-7 -> 7e-7 -> 4e-6 on six tets; the binary32 contraction stays at
-// 1e-7.)  Larger extents, vanishing cuts and strengths that do not fit keep
-// the binary32 contraction (xs = 0).
+// 1e-7.)  Larger extents, vanishing cuts and meshes whose largest strength is
+// below 1e-25 or not below 1e25 keep the binary32 contraction (xs = 0).
 void split_scales(const bs_mesh *m, double cut, double eps, bsk::Thresholds &th)
 {
     th.xs = th.ws = th.d2_g1 = th.d2_amb = 0.f;
-    if (!(cut > 1e-12) || !(cut < 1e12) || !(eps < 0.5) || !(m->extent <= 32.0 * cut) || !(m->max_w < 1e25)) return;
+    if (!(cut > 1e-12) || !(cut < 1e12) || !(eps < 0.5) || !(m->extent <= 32.0 * cut)) return;
+    if (!(m->max_w < 1e25) || (m->max_w < 1e-25 && m->max_w > 0.0)) return; // (ws: at most 2^97)
     int k = 0;
     std::frexp(cut, &k); // cut in [2^(k-1), 2^k)
     const double xs = std::ldexp(1.0, -k - 4);
-    const double top = std::max(m->max_w, 1e-25) * std::max(1.0, m->extent * xs);
+    const double top = (m->max_w > 0.0 ? m->max_w : 1.0) * std::max(1.0, m->extent * xs);
     int kw = 0;
     std::frexp(top, &kw); // top < 2^kw
     th.xs = (float)xs;

@@ -50,3 +50,20 @@ def test_targets_far_from_every_tet(cells, cut, far):
         e = np.linalg.norm(v - ref) / np.linalg.norm(magnitudes(x, om, m.tets, pts))
         print(f"  {m.n_tets} tets, {far} cuts of {cut}: error {e:.2e} of the terms", flush=True)
         assert e <= 3e-7, e
+
+
+@pytest.mark.parametrize("exponent", [-22, -24, -26, -28, -31, -34])
+def test_weak_vorticity(exponent):
+    """Velocities are linear in the vorticity down to the end of binary32's
+    normal range (relative L2 1e-6, as for vorticity of order one)."""
+    m = W.make_config("C1", scale=(8, 7, 6))
+    cuts = dict(near_cut=0.5, d_g11=0.75, d_g4=1.0)
+    om = m.omega * 10.0 ** exponent
+    h = bs.bs_mesh_upload(m.xyz, om, m.tets)
+    fixed(h, **cuts)
+    v = bs.bs_eval_velocity(h)
+    bs.bs_mesh_free(h)
+    ref = oracle.evaluate(m.xyz, om, m.tets, oracle.make_policy("fixed", **cuts))
+    e = np.linalg.norm((v - ref) * 10.0 ** -exponent) / np.linalg.norm(ref * 10.0 ** -exponent)
+    print(f"  vorticity 1e{exponent}: rel-L2 {e:.2e}", flush=True)
+    assert e <= 1e-6, e
