@@ -274,7 +274,7 @@ struct bs_mesh {
     std::vector<double> xyz, omega; // current FP64 inputs
     double hbar = 0.0, max_vc = 0.0;
     double max_abs = 0.0; // largest coordinate magnitude of any node or evaluation point
-    double extent = 0.0;  // diagonal of the bounding box of the nodes and evaluation points
+    double extent[2] = {0.0, 0.0}; // diagonal of the bounding box of the nodes; of the nodes and evaluation points
     double max_w = 0.0;   // largest magnitude of any component of a Gauss point's strength
     int64_t reoriented = 0;
     std::vector<int8_t> orient; // sign of det per tet at upload (inversion check on updates)
@@ -1067,7 +1067,12 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
     std::vector<float> xh((size_t)3 * npad), xl((size_t)3 * npad), om((size_t)3 * npad);
     double max_abs = 0.0;
     double xlo[3] = {1e300, 1e300, 1e300}, xhi[3] = {-1e300, -1e300, -1e300};
+    auto diagonal = [&] {
+        return std::sqrt((xhi[0] - xlo[0]) * (xhi[0] - xlo[0]) + (xhi[1] - xlo[1]) * (xhi[1] - xlo[1]) +
+                         (xhi[2] - xlo[2]) * (xhi[2] - xlo[2]));
+    };
     for (int64_t p = 0; p < npad; ++p) {
+        if (p == n) m->extent[0] = diagonal();
         const bool is_t = p >= t0 && p < t0 + tn;
         const int64_t i = p < n ? orig[(size_t)p] : is_t ? torig[(size_t)(p - t0)] : (n > 0 ? orig[0] : 0);
         for (int c = 0; c < 3; ++c) {
@@ -1146,9 +1151,8 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
     }
     m->max_vc = max_vc;
     m->max_abs = max_abs;
-    m->extent = npad > 0 ? std::sqrt((xhi[0] - xlo[0]) * (xhi[0] - xlo[0]) + (xhi[1] - xlo[1]) * (xhi[1] - xlo[1]) +
-                                     (xhi[2] - xlo[2]) * (xhi[2] - xlo[2]))
-                         : 0.0;
+    if (npad == n) m->extent[0] = diagonal();
+    m->extent[1] = diagonal();
     bsk::Bins bins{};
     double cs = 2.0 * (m->hbar > 0 ? m->hbar : 1.0);
     if (T > 0) {
@@ -1855,17 +1859,20 @@ struct EvalBufs {
 // 2), whatever pairs a target has.  (At 64 cuts a target with no pair near the
 // cut would lose up to 3 bits, at 128 cuts 6: its velocity's relative error
 // grew 1e-7 -> 7e-7 -> 4e-6 on six tets; the binary32 contraction stays at
-// 1e-7.)  Larger extents, vanishing cuts and meshes whose largest strength is
-// below 1e-25 or not below 1e25 keep the binary32 contraction (xs = 0).
-void split_scales(const bs_mesh *m, double cut, double eps, bsk::Thresholds &th)
+// 1e-7.)  The extent is that of the targets evaluated and the mesh: points
+// kept from an earlier bs_eval_points do not count for the nodes.  Larger
+// extents, vanishing cuts and meshes whose largest strength is below 1e-25 or
+// not below 1e25 keep the binary32 contraction (xs = 0).
+void split_scales(const bs_mesh *m, bool targets, double cut, double eps, bsk::Thresholds &th)
 {
+    const double extent = m->extent[targets ? 1 : 0];
     th.xs = th.ws = th.d2_g1 = th.d2_amb = 0.f;
-    if (!(cut > 1e-12) || !(cut < 1e12) || !(eps < 0.5) || !(m->extent <= 32.0 * cut)) return;
+    if (!(cut > 1e-12) || !(cut < 1e12) || !(eps < 0.5) || !(extent <= 32.0 * cut)) return;
     if (!(m->max_w < 1e25) || (m->max_w < 1e-25 && m->max_w > 0.0)) return; // (ws: at most 2^97)
     int k = 0;
     std::frexp(cut, &k); // cut in [2^(k-1), 2^k)
     const double xs = std::ldexp(1.0, -k - 4);
-    const double top = (m->max_w > 0.0 ? m->max_w : 1.0) * std::max(1.0, m->extent * xs);
+    const double top = (m->max_w > 0.0 ? m->max_w : 1.0) * std::max(1.0, extent * xs);
     int kw = 0;
     std::frexp(top, &kw); // top < 2^kw
     th.xs = (float)xs;
@@ -1938,7 +1945,7 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, double *out2 = nullptr,
             th.s_g1 = 0.f;
             th.s_amb = INFINITY;
         }
-        split_scales(m, c_4, eps, th);
+        split_scales(m, targets, c_4, eps, th);
     }
     bsk::AngTab ang{};
     ang.dir = (const float4 *)m->dir.p;

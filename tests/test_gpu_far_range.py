@@ -67,3 +67,19 @@ def test_weak_vorticity(exponent):
     e = np.linalg.norm((v - ref) * 10.0 ** -exponent) / np.linalg.norm(ref * 10.0 ** -exponent)
     print(f"  vorticity 1e{exponent}: rel-L2 {e:.2e}", flush=True)
     assert e <= 1e-6, e
+
+
+@pytest.mark.parametrize("far", [3.0, 10.0, 20.0, 40.0, 1000.0])
+def test_nodes_after_points(far):
+    """Evaluation points stay with the mesh; wherever they lie, the nodes' own
+    velocities are the same bits after them as before."""
+    m = W.make_config("C1", scale=(8, 7, 6))
+    cuts = dict(near_cut=0.5, d_g11=0.75, d_g4=1.0)
+    cut = oracle.mean_edge(m.xyz, m.tets)
+    h = bs.bs_mesh_upload(m.xyz, m.omega, m.tets)
+    fixed(h, **cuts)
+    v0 = bs.bs_eval_velocity(h)
+    bs.bs_eval_points(h, np.array([[far * cut, 0.1, -0.2], [0.3, 0.2, 0.1]]))
+    v1 = bs.bs_eval_velocity(h)
+    bs.bs_mesh_free(h)
+    assert np.array_equal(v0, v1), np.abs(v0 - v1).max()
