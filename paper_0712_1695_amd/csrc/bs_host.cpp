@@ -1855,23 +1855,24 @@ struct EvalBufs {
 // `cut`, whose scaled distance is at least 2^-5, so that d^-3 <= 2^15, and
 // for strengths times offsets up to 2^15: both fit binary16.  eps: relative
 // margin on d^2 around the cut.  A binary16 pair holds 23 bits of a value of
-// at least 2^-3; d^-3 stays above that out to 32 cuts (scaled distances up to
-// 2), whatever pairs a target has.  (At 64 cuts a target with no pair near the
-// cut would lose up to 3 bits, at 128 cuts 6: its velocity's relative error
-// grew 1e-7 -> 7e-7 -> 4e-6 on six tets; the binary32 contraction stays at
-// 1e-7.)  The extent is that of the targets evaluated and the mesh: points
-// kept from an earlier bs_eval_points do not count for the nodes.  Larger
+// at least 2^-3; d^-3 stays above that out to scaled distances of 2 (32 to 64
+// cuts), whatever pairs a target has.  (Further out a target with no pair near
+// the cut loses bits: six tets 64 cuts of scaled length 2^-4 away had 7e-7
+// relative error, 125 cuts 4e-6; the binary32 contraction stays at 1e-7.)  The
+// extent is that of the targets evaluated and the mesh: points kept from an
+// earlier bs_eval_points do not count for the nodes.  Larger
 // extents, vanishing cuts and meshes whose largest strength is below 1e-25 or
 // not below 1e25 keep the binary32 contraction (xs = 0).
 void split_scales(const bs_mesh *m, bool targets, double cut, double eps, bsk::Thresholds &th)
 {
     const double extent = m->extent[targets ? 1 : 0];
     th.xs = th.ws = th.d2_g1 = th.d2_amb = 0.f;
-    if (!(cut > 1e-12) || !(cut < 1e12) || !(eps < 0.5) || !(extent <= 32.0 * cut)) return;
+    if (!(cut > 1e-12) || !(cut < 1e12) || !(eps < 0.5)) return;
     if (!(m->max_w < 1e25) || (m->max_w < 1e-25 && m->max_w > 0.0)) return; // (ws: at most 2^97)
     int k = 0;
     std::frexp(cut, &k); // cut in [2^(k-1), 2^k)
     const double xs = std::ldexp(1.0, -k - 4);
+    if (!(extent * xs <= 2.0)) return;
     const double top = (m->max_w > 0.0 ? m->max_w : 1.0) * std::max(1.0, extent * xs);
     int kw = 0;
     std::frexp(top, &kw); // top < 2^kw
