@@ -1819,7 +1819,9 @@ int far_splits(const bs_mesh *m)
 // 1,792 of its workgroups (seven waves per SIMD) and blocks differ in cost,
 // so a block's tets are split until the launch has twelve rounds, four-fold at
 // least, 32-fold at most (there a wave of the smallest meshes has two or three
-// pieces left).  Band kernel alone, one workgroup per block against this: 21
+// pieces left), and no further than leaves each of a workgroup's four waves
+// two 32-tet pieces (about 55 tets per cubic mean edge times 4 pi / 3: cuts
+// of one edge or less have a few dozen pieces).  Band kernel alone, one workgroup per block against this: 21
 // blocks (10^3 box) 1.96 -> 0.12 ms, 313 blocks (20,011 points) 9.5 -> 2.1,
 // 1,519 (ring) 15.0 -> 10.1, 1,839 (Fourier field) 18.8 -> 13.0, 8,304 (two
 // rings) 71 -> 62 ms; beyond, the partial sums cost more than the balance
@@ -1829,7 +1831,10 @@ int band_splits(const bs_mesh *m, int64_t nblk)
     const bs_policy &P = m->pol;
     const bool fixed_like = P.kind == BS_POLICY_FIXED || P.kind == BS_POLICY_LEARNED;
     if (!fixed_like || nblk <= 0 || !(far_on_matrix_cores(m) || uses_treecode(P))) return 1;
-    return (int)std::min<int64_t>(32, std::max<int64_t>(4, 12 * 1792 / nblk));
+    const double hb = std::max(m->hbar, 1e-300);
+    const double r = std::max(P.d_g4, m->max_vc / hb) + 2.0; // reach of a block's band, block included, in mean edges
+    const int64_t most = (int64_t)std::min(32.0, std::max(1.0, 55.0 / 32.0 * r * r * r / 8.0));
+    return (int)std::min<int64_t>(most, std::max<int64_t>(4, 12 * 1792 / nblk));
 }
 
 // Workgroups (waves) per node of the ray-tracing walk: the chip holds 4,096 of
