@@ -284,7 +284,7 @@ struct bs_mesh {
     std::vector<int32_t> nbr_in;  // [T][4] face neighbours (input tet numbering, -1 boundary)
     std::vector<int32_t> inc_in_start, inc_in_list; // corners 4t + j of every input node, by node (built once)
     std::vector<int64_t> edge_keys; // unique edges, sorted (lo * (n + 1) + hi); built on first use
-    DBuf x64, tord, slots, tin; // inputs of the record kernel (FP64 positions, tet order, node slots, connectivity)
+    DBuf x64, tord, slots, tin; // inputs of the record kernels (FP64 positions, tet order, node slots, connectivity)
     DBuf found; // what the kernels of a build find: max_w's bits, nheld
     bool manifold = true;         // every face shared by at most two tets, one on each side
     bool convex = false;          // boundary is one closed, locally convex surface (rays never re-enter)
@@ -319,8 +319,7 @@ struct bs_mesh {
         int64_t exp_nodes = 0, dir_nodes = 0, exp_pts = 0, dir_pts = 0; // expansion terms, direct pairs
         int64_t cov_nodes = 0, cov_pts = 0; // pairs the expansions sum
         DBuf nrange, child, leaves, c64, crec, src64, g1t, tidt, M, N, acc_start, acc, dir_start, dir;
-        DBuf torder, tin, x64, rank; // tree order, input connectivity, FP64 positions, node slots (device)
-        bool tin_valid = false;      // the connectivity is on the device (it never changes)
+        DBuf torder; // tree order (device)
     } tree;
     std::vector<int32_t> h_torig; // evaluation points in their k-d order (host copy)
     int rt_mode = 0; // 0: walk (face-manifold meshes), 1: always the candidate kernel
@@ -939,8 +938,7 @@ int build_tree_plan(bs_mesh *m, hipStream_t s)
         (rc = dalloc(tp.leaves, 4 * leaves.size())) || (rc = dalloc(tp.c64, 8 * c64.size())) ||
         (rc = dalloc(tp.crec, 4 * crec.size())) || (rc = dalloc(tp.src64, 8 * 8 * (size_t)T)) ||
         (rc = dalloc(tp.g1t, 4 * 8 * (size_t)T)) || (rc = dalloc(tp.tidt, sizeof(int4) * (size_t)T)) ||
-        (rc = dalloc(tp.torder, 4 * (size_t)T)) || (rc = dalloc(tp.tin, 16 * (size_t)T)) ||
-        (rc = dalloc(tp.x64, 8 * 3 * (size_t)n)) || (rc = dalloc(tp.rank, 4 * (size_t)n)) ||
+        (rc = dalloc(tp.torder, 4 * (size_t)T)) ||
         (rc = dalloc(tp.M, 8 * 3 * (size_t)nnode * NK)) || (rc = dalloc(tp.N, 4 * 3 * (size_t)nnode * NC)) ||
         (rc = dalloc(tp.acc_start, 4 * acc_start.size())) || (rc = dalloc(tp.acc, 4 * acc_list.size())) ||
         (rc = dalloc(tp.dir_start, 4 * dir_start.size())) || (rc = dalloc(tp.dir, 4 * dir_list.size())))
@@ -956,19 +954,13 @@ int build_tree_plan(bs_mesh *m, hipStream_t s)
     BS_UP(c64, c64)
     BS_UP(crec, crec)
     BS_UP(torder, order)
-    BS_UP(x64, m->xyz)
-    BS_UP(rank, m->h_rank)
-    if (!tp.tin_valid) {
-        BS_UP(tin, m->tets)
-        tp.tin_valid = true;
-    }
     BS_UP(acc_start, acc_start)
     BS_UP(acc, acc_list)
     BS_UP(dir_start, dir_start)
     BS_UP(dir, dir_list)
 #undef BS_UP
-    if ((e = bsk::launch_tree_sources((int)T, (const int *)tp.torder.p, (const int4 *)tp.tin.p, (const double *)tp.x64.p,
-                                      (const double *)m->om64.p, (const int *)tp.rank.p, (double *)tp.src64.p,
+    if ((e = bsk::launch_tree_sources((int)T, (const int *)tp.torder.p, (const int4 *)m->tin.p, (const double *)m->x64.p,
+                                      (const double *)m->om64.p, (const int *)m->slots.p, (double *)tp.src64.p,
                                       (float *)tp.g1t.p, (int4 *)tp.tidt.p, s)))
         return hip_fail(e, "treecode sources");
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "upload tree");
@@ -1740,8 +1732,7 @@ void bs_mesh_free(bs_mesh *m)
                     &m->gvel, &m->tgrad, &m->ngrad, &m->om64, &m->srate,
                     &m->tree.nrange, &m->tree.child, &m->tree.leaves, &m->tree.c64, &m->tree.crec,
                     &m->tree.src64, &m->tree.g1t, &m->tree.tidt, &m->tree.M, &m->tree.N, &m->tree.acc_start,
-                    &m->tree.acc, &m->tree.dir_start, &m->tree.dir, &m->tree.torder, &m->tree.tin, &m->tree.x64,
-                    &m->tree.rank, &m->x64, &m->tord, &m->slots, &m->tin, &m->found, &m->held};
+                    &m->tree.acc, &m->tree.dir_start, &m->tree.dir, &m->tree.torder, &m->x64, &m->tord, &m->slots, &m->tin, &m->found, &m->held};
     for (DBuf *b : bufs) dfree(*b);
     for (auto &a : m->aux)
         if (a) (void)hipStreamSynchronize(a);
@@ -2079,17 +2070,17 @@ int eval_device(bs_mesh *m, hipStream_t s, bool targets, double *out2 = nullptr,
 
 // Bytes of scratch an evaluation of the nodes needs under the current
 // policy and far-field mode with nsplit band splits, laid out (256-byte
-// aligned) as part, band, rtv, counters, non-finite flag, fallback list,
-// learned lists; offsets in off[7].
-size_t eval_scratch_layout(const bs_mesh *m, int nsplit, size_t off[7])
+// aligned) as part, band, rtv, counters, the walk's node list, learned lists;
+// offsets in off[6].
+size_t eval_scratch_layout(const bs_mesh *m, int nsplit, size_t off[6])
 {
     auto al = [](size_t v) { return (v + 255) / 256 * 256; };
     const size_t np = (size_t)m->npad, nn = (size_t)m->n;
-    const size_t sz[7] = {8 * 3 * np * (size_t)far_splits(m), 8 * 3 * np * (size_t)nsplit, 8 * 3 * np * (size_t)walk_waves(m),
-                          8 * (size_t)bsk::kCntWords, 4, 4 * (nn + 1),
+    const size_t sz[6] = {8 * 3 * np * (size_t)far_splits(m), 8 * 3 * np * (size_t)nsplit, 8 * 3 * np * (size_t)walk_waves(m),
+                          8 * (size_t)bsk::kCntWords, 4 * nn,
                           m->pol.kind == BS_POLICY_LEARNED ? 4 * (nn * bsk::kSelListCap + 5 * nn) : 0};
     size_t o = 0;
-    for (int k = 0; k < 7; ++k) {
+    for (int k = 0; k < 6; ++k) {
         off[k] = o;
         o += al(sz[k]);
     }
@@ -2306,7 +2297,7 @@ int bs_eval_velocity_noalloc(bs_mesh *m, double *vel, uint32_t flags, void *stre
     char *base = (char *)bsk::scratch_ptr(m->device);
     if (!base) return fail(BS_E_DEVICE, "the static scratch of device %d is not available", m->device);
     m->far_mode = (flags & BS_EVAL_VALU_FAR) ? 1 : 0;
-    size_t off[7];
+    size_t off[6];
     // (band splits that the scratch cannot hold are given up)
     int nsplit = band_splits(m, m->nblk);
     size_t need = eval_scratch_layout(m, nsplit, off);
@@ -2322,8 +2313,8 @@ int bs_eval_velocity_noalloc(bs_mesh *m, double *vel, uint32_t flags, void *stre
     g.band = (double *)(base + off[1]);
     g.rtv = (double *)(base + off[2]);
     g.cnt = (unsigned long long *)(base + off[3]);
-    g.fallback = (int *)(base + off[5]);
-    g.sel = m->pol.kind == BS_POLICY_LEARNED ? (int *)(base + off[6]) : nullptr;
+    g.fallback = (int *)(base + off[4]);
+    g.sel = m->pol.kind == BS_POLICY_LEARNED ? (int *)(base + off[5]) : nullptr;
     g.vel = vel;
     const int rc = eval_device(m, (hipStream_t)stream, false, nullptr, &g);
     m->far_mode = 0;
