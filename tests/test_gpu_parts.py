@@ -156,3 +156,28 @@ def test_folded_faces(kind, notch):
         ref = oracle.evaluate(xyz, om, tets, pol)
     print(f"  {kind} notch {notch}: rel-L2 {rel(v, ref):.2e}", flush=True)
     assert rel(v, ref) <= 1e-6, rel(v, ref)
+
+
+@pytest.mark.parametrize("kind", ["pure", "fixed", "learned"])
+def test_parts_brought_into_contact(kind):
+    """Moving two parts together gives the velocities of the touching mesh
+    uploaded as it is, and the call without allocations the same ones."""
+    import torch
+
+    xyz, om, tets = joined()
+    i = np.arange(343) % 7
+    x, o, t, _ = doubled(xyz, om, tets, i[tets].max(axis=1) > 3, np.nonzero(i == 3)[0])
+    want, _ = evaluate(x, o, t, kind)
+    apart = x.copy()
+    apart[np.unique(t[i[tets].max(axis=1) > 3])] += [0.25, 0.0, 0.0]
+    h = bs.bs_mesh_upload(apart, o, t)
+    bs.bs_set_policy(h, **policy(kind))
+    bs.bs_eval_velocity(h)
+    bs.bs_mesh_update(h, xyz=x)
+    v, st = bs.bs_eval_velocity(h, stats=True)
+    out = torch.empty((len(x), 3), dtype=torch.float64, device="cuda")
+    bs.bs_eval_velocity_noalloc(h, out)
+    got = out.cpu().numpy()
+    bs.bs_mesh_free(h)
+    # (the order of the sums may differ between the calls: binary32 rounding)
+    assert st["rt_candidate_nodes"] > 98 and rel(v, want) <= 1e-7 and rel(got, want) <= 1e-7
