@@ -55,8 +55,9 @@ extern "C" {
 #define BS_PTR_DEVICE 1u
 /* bs_eval_velocity only: take the far field of the fixed-rule policies on
  * the vector ALUs (every pair by the 1-point rule, then the G1 term of the
- * other pairs removed) instead of the matrix cores (G1 pairs only, FP32
- * MFMA contractions).  Both compute the same sum; for comparison. */
+ * other pairs removed) instead of the matrix cores (G1 pairs only; factors
+ * as 16-bit pieces, or in FP32 where the mesh's range does not fit them).
+ * Both compute the same sum; for comparison. */
 #define BS_EVAL_VALU_FAR 0x10u
 /* bs_eval_velocity only: run every kernel on the given stream, one after
  * another, instead of the band and ray-tracing kernels on two library

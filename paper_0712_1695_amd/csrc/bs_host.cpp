@@ -1785,7 +1785,7 @@ bool far_on_matrix_cores(const bs_mesh *m)
 
 // Tet splits of the all-pairs Gauss kernels (0: no far-field kernel).  The
 // matrix-core kernel: eight (one eighth of the tets per XCD, see
-// k_far_mfma), times the number of sub-splits that keeps each split's
+// far_item), times the number of sub-splits that keeps each split's
 // 32-byte records within 3 MiB of an XCD's 4 MiB L2.  The vector-ALU kernel:
 // enough waves to fill 256 CUs.
 int far_splits(const bs_mesh *m)

@@ -25,12 +25,22 @@
 // Kernels:
 //   k_gauss_all  every pair by one Gauss rule (G1 for the fixed policy:
 //                the far field of all pairs), tet records wave-uniform;
-//   k_far_mfma   the G1 pairs of the fixed rule on the matrix cores (FP32
-//                MFMA; pairs with another rule masked out);
-//   k_band_piece per 64-node block: pairs whose fixed rule is G4 / G11,
-//                after k_far_mfma (row pieces staged in LDS);
+//   k_far_split  the G1 pairs of the fixed rule on the matrix cores (pairs
+//                with another rule masked out), both contractions on 16-bit
+//                instructions;
+//   k_far_mfma   the same on FP32 MFMA, where the 16-bit pieces do not hold
+//                the mesh's range;
+//   k_band_piece per 64-node block: pairs whose fixed rule is G4 / G11, where
+//                the far field leaves them out (k_far_split, k_far_mfma, the
+//                treecode; row pieces staged in LDS);
 //   k_band       the same after k_gauss_all, also removing their G1 term;
-//   k_rt         one wave per node: ray tracing of its near tetrahedra;
+//   k_select     the learned policy's choice for every near pair;
+//   k_rt_walk    ray tracing from tet to tet across face neighbours;
+//   k_rt_reenter the parts of the rays that enter the mesh again;
+//   k_rt         one wave per node: ray tracing of its near tetrahedra one by
+//                one (nodes and points the walk cannot start from, meshes
+//                that are not face-manifold);
+//   k_nodes_held the nodes in or on a tet they are no vertex of;
 //   k_combine    FP64 sum of the partials, back to input node order.
 #include "bs_internal.h"
 #include "bs_mlp_dev.h"
@@ -717,10 +727,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
 // against the block's four node tiles; a unit's sums are added in binary32 and
 // folded into the workgroup's compensated sums every fourth chunk (eight
 // additions), the waves in turn.  Two-ring mesh (531,441 nodes, 3,072,000
-// tets): 428 ms against k_far_mfma's 508.  Bound by issue: per 1024 pairs and
-// SIMD about 390 cycles of vector instructions for the cubes and their pieces,
-// 30 for the sums, 192 of MFMA, 110 for preparing the operands, partly
-// overlapped (660 in all).  Relative L2 error against the FP64 oracle (fixed
+// tets): 428 ms against k_far_mfma's 508.  Bound by issue: per 1024 pairs a
+// SIMD issues 133 vector instructions, 16 of them reciprocal square roots (the
+// cubes and their pieces about 390 cycles by the instructions' rates, the sums
+// 30, preparing the operands 110), and its matrix pipe is busy 192 cycles; they
+// overlap in part, 655 in all.  Relative L2 error against the FP64 oracle (fixed
 // rule, all kernels; k_far_mfma in brackets): ring 6.50e-8 (6.71e-8), two
 // rings 5.78e-8 (6.01e-8), Fourier field 8.69e-8 (8.63e-8), swirl 4.94e-8
 // (4.94e-8); 2,058 tets seen from 4 to 30 cuts away 2.1 to 4.4e-8 (2.4 to
@@ -996,8 +1007,8 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
 // sphere, lanes whose pair rule is not G1 subtract that G1 term, then lanes
 // with G4 / G11 add that rule (ray-traced pairs are added by the ray-tracing
 // kernels).  The waves' partial sums are combined in FP64 through LDS.
-// (After k_far_mfma, which leaves out every pair that is not G1, the band
-// runs in k_band_piece.)
+// (After the matrix-core far field or the treecode, which leave out every pair
+// that is not G1, the band runs in k_band_piece.)
 constexpr int kBandWaves = 4;
 
 template <int PREC>
@@ -1110,7 +1121,8 @@ __global__ void __launch_bounds__(64 * kBandWaves) k_band(DevMesh m, Thresholds 
     }
 }
 
-// Band pairs after k_far_mfma (no G1 terms to remove): k_band's blocks and
+// Band pairs where the far field holds no G1 term of theirs (the matrix-core
+// kernels, the treecode): k_band's blocks and
 // rule masks, but each wave takes pieces of 32 tets of the block's rows,
 // staged in its own LDS.  The centroids and G4 points of the next piece
 // are loaded into registers while the current piece is evaluated, so a tet
@@ -1941,10 +1953,13 @@ __device__ __forceinline__ void list_shift(int *list, int &n, int used, int lane
     n = rest;
 }
 
-// workgroups of k_rt over a node list: two rounds of the chip's wave slots
-// at this kernel's four waves per SIMD (the walk's fallback on a moved
-// mesh is about 30% of the nodes), few enough that an empty list costs
-// nothing beside the kernels that run concurrently
+// workgroups of k_rt and k_rt_reenter over a node list whose length only the
+// device knows: two rounds of the chip's wave slots at four waves per SIMD
+// (k_rt; k_rt_reenter has three or four), few enough that a short list costs
+// little beside the kernels that run concurrently.  k_rt's list holds the
+// nodes the walk cannot start from (usually none), or the points outside the
+// mesh or next to a face; k_rt_reenter's the nodes with rays that leave early,
+// about 30% on a moved mesh
 constexpr int kRtListGrid = 8192;
 
 template <int PREC, bool LEARNED>
@@ -2076,9 +2091,10 @@ __global__ void __launch_bounds__(64) k_rt(DevMesh m, Thresholds th, AngTab ang,
 
 // ---------------------------------------------------------------------------
 // Ray tracing by walking the mesh (face-manifold meshes: every interior
-// face shared by two tets).  Where the boundary is not convex a ray that
-// leaves the mesh may enter it again, so a node with a ray that leaves
-// before its stop distance (or starts outside) is listed for k_rt_reenter.
+// face shared by two tets, one on each side).  Where the boundary is not
+// convex a ray that leaves the mesh may enter it again, so a node with a ray
+// that leaves before its stop distance (or starts outside) is listed for
+// k_rt_reenter; a node in or on a tet it is no vertex of is left to k_rt.
 // One wave per node; lane = ray.  Every ray leaves the node through the one
 // incident tet whose opposite face it crosses, then crosses face neighbours
 // outward: the exit face of one tet is the entry face of the next, decided
