@@ -1229,8 +1229,9 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
             return hip_fail(e, "Gauss records");
         }
     }
-    // nodes in or on other tets: where the boundary is not convex, known only
-    // at the end (so already now unless it was convex the last time)
+    // nodes in or on other tets: only where the boundary is not convex, which is
+    // known at the end (already now, beside the host's part, if it was not the
+    // last time)
     auto find_held = [&]() -> int {
         const float reach = (float)(max_vc * (1.0 + 1e-4) + 16.0 * std::ldexp(1.0, -24) * max_abs);
         const hipError_t e = bsk::launch_nodes_held(
@@ -1242,7 +1243,7 @@ int build_device_mesh(bs_mesh *m, hipStream_t s)
         (void)hipStreamSynchronize(s);
         return r;
     };
-    const bool held_known = T > 0 && m->manifold && !m->convex; // (m->convex: of the last build)
+    const bool held_known = m->nbface > 0; // (of the last build)
     if (held_known && (rc = find_held())) return wait_records(rc);
 
     // ---- bounding sphere of the binary32 centroids of every tile of 16
